@@ -199,13 +199,18 @@ Layout layout(const slw_model_cfg& c, int C, int B) {
     return L;
 }
 
-size_t gemm_partial_bytes(const slw_model_cfg& c, int M) {
-    size_t b = 0;
-    b = std::max(b, plan_gemm(M, qkv_width(c), c.d_model).partial_bytes);
-    b = std::max(b, plan_gemm(M, c.d_model, c.n_q_heads * c.head_dim).partial_bytes);
-    b = std::max(b, plan_gemm(M, 2 * c.ffn_dim, c.d_model).partial_bytes);
-    b = std::max(b, plan_gemm(M, c.d_model, c.ffn_dim).partial_bytes);
-    return b;
+// GEMM plans of a layer's four projections at M rows.
+struct LayerPlans {
+    GemmPlan qkv, o, gu, d;
+    size_t partial_bytes() const {
+        return std::max(std::max(qkv.partial_bytes, o.partial_bytes), std::max(gu.partial_bytes, d.partial_bytes));
+    }
+};
+
+LayerPlans plan_layer(const slw_model_cfg& c, int M, int max_splits = kMaxSplits) {
+    return {plan_gemm(M, qkv_width(c), c.d_model, max_splits),
+            plan_gemm(M, c.d_model, c.n_q_heads * c.head_dim, max_splits),
+            plan_gemm(M, 2 * c.ffn_dim, c.d_model, max_splits), plan_gemm(M, c.d_model, c.ffn_dim, max_splits)};
 }
 
 int check_cfg(const slw_model_cfg& c) {
@@ -287,7 +292,7 @@ int ensure_stage_events(slw_ctx* ctx) {
 }
 
 int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void* x_out, void* ws,
-                      const Layout& L, hipStream_t stream, bool no_alloc);
+                      const Layout& L, const LayerPlans& plans, hipStream_t stream, bool no_alloc);
 
 // One iteration: validation, KV reservation (all or nothing), then the
 // metadata, its upload and the kernels.  A failure after the reservation
@@ -359,7 +364,11 @@ int mixed_iteration_impl(slw_ctx* ctx, const slw_batch* bt, const void* x_in, vo
         }
     }
     const Layout L = layout(c, C, B);
-    const size_t gpart = gemm_partial_bytes(c, C + B);
+    LayerPlans plans = plan_layer(c, C + B);
+    // the static array also takes an iteration whose split-K partials alone
+    // would not fit, with the products unsplit
+    if (no_alloc && ws_bytes < L.end_fixed + plans.partial_bytes()) plans = plan_layer(c, C + B, 1);
+    const size_t gpart = plans.partial_bytes();
     if (ws_bytes < L.end_fixed + gpart)
         return fail(SLW_ENOMEM, "%s holds %zu bytes, this iteration needs %zu",
                     no_alloc ? "the static workspace (SLW_STATIC_WS_BYTES)" : "the workspace", ws_bytes,
@@ -376,7 +385,7 @@ int mixed_iteration_impl(slw_ctx* ctx, const slw_batch* bt, const void* x_in, vo
     KvManager::Undo undo;
     rc = ctx->kv.reserve_all(req, &undo);
     if (rc) return rc;
-    rc = enqueue_iteration(ctx, bt, x_in, x_out, ws, L, stream, no_alloc);
+    rc = enqueue_iteration(ctx, bt, x_in, x_out, ws, L, plans, stream, no_alloc);
     if (rc) ctx->kv.rollback(undo);
     return rc;
 }
@@ -562,7 +571,7 @@ int plan_chunk(const slw_model_cfg& c, int C, const std::vector<int32_t>& qt_pos
 }
 
 int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void* x_out, void* ws,
-                      const Layout& L, hipStream_t stream, bool no_alloc) {
+                      const Layout& L, const LayerPlans& plans, hipStream_t stream, bool no_alloc) {
     const slw_model_cfg& c = ctx->cfg;
     const int C = bt->C, B = bt->B;
     const std::vector<Prefill>& pre = ctx->prefills;
@@ -692,10 +701,6 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
 
     const int d = c.d_model, hq = c.n_q_heads, hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
     const int qw = qkv_width(c);
-    const GemmPlan p_qkv = plan_gemm(M, qw, d);
-    const GemmPlan p_o = plan_gemm(M, d, hq * hd);
-    const GemmPlan p_gu = plan_gemm(M, 2 * F, d);
-    const GemmPlan p_d = plan_gemm(M, d, F);
     const size_t layer_pool = static_cast<size_t>(ctx->kv.num_blocks()) * hkv * hd * 16 * 2;
 
     const bool timing = !no_alloc && ctx->stage_depth > 0;
@@ -731,7 +736,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
             ga.hq = hq;
             ga.hkv = hkv;
             ga.hd = hd;
-            launch_gemm(ga, p_qkv, gpartp, stream);
+            launch_gemm(ga, plans.qkv, gpartp, stream);
         }
         if ((rc = mark(l, 3))) return rc;
         // Both attentions in one launch, or on two streams for a long
@@ -806,14 +811,14 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         if ((rc = mark(l, 5))) return rc;
         launch_attention_merge(&ca, &da, stream);
         if ((rc = mark(l, 6))) return rc;
-        launch_gemm(GemmArgs{attn, wl.wo, hbuf, cur, M, d, hq * hd, hq * hd, d, EPI_RESID_F32OUT}, p_o, gpartp,
+        launch_gemm(GemmArgs{attn, wl.wo, hbuf, cur, M, d, hq * hd, hq * hd, d, EPI_RESID_F32OUT}, plans.o, gpartp,
                     stream);
         if ((rc = mark(l, 7))) return rc;
         launch_rmsnorm(hbuf, true, wl.g2, xn, M, d, c.rms_eps, stream);
         if ((rc = mark(l, 8))) return rc;
-        launch_gemm(GemmArgs{xn, wl.wgu, act, nullptr, M, 2 * F, d, d, F, EPI_SWIGLU}, p_gu, gpartp, stream);
+        launch_gemm(GemmArgs{xn, wl.wgu, act, nullptr, M, 2 * F, d, d, F, EPI_SWIGLU}, plans.gu, gpartp, stream);
         if ((rc = mark(l, 9))) return rc;
-        launch_gemm(GemmArgs{act, wl.wd, x_out, hbuf, M, d, F, F, d, EPI_RESID_F32IN}, p_d, gpartp, stream);
+        launch_gemm(GemmArgs{act, wl.wd, x_out, hbuf, M, d, F, F, d, EPI_RESID_F32IN}, plans.d, gpartp, stream);
         if ((rc = mark(l, 10))) return rc;
     }
     HIP_TRY(hipGetLastError());
@@ -915,7 +920,7 @@ extern "C" int slw_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t out[6]) {
     if (m < 1 || n < 128 || n % 128 || k < 64 || k % 64)
         return fail(SLW_EINVAL, "m >= 1, n a multiple of 128 and k of 64 (got %d, %d, %d)", m, n, k);
     const GemmPlan p = plan_gemm(m, n, k);
-    const int32_t v[6] = {p.cfg, p.bm, p.bn, p.splits, p.sk_workers, p.dp_tiles};
+    const int32_t v[6] = {p.cfg, p.bm, p.bn, p.splits, 0, 0};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
     return SLW_OK;
 }
@@ -998,7 +1003,10 @@ extern "C" int slw_workspace_size(slw_ctx* ctx, int32_t max_C, int32_t max_B, si
         if (!ctx || !bytes) return fail(SLW_EINVAL, "null argument");
         if (max_C < 0 || max_B < 0) return fail(SLW_EINVAL, "negative size");
         size_t gp = 0;
-        for (int m = 1; m <= max_C + max_B; ++m) gp = std::max(gp, gemm_partial_bytes(ctx->cfg, m));
+        // plans are the same for all row counts of a block of 32 (past the
+        // narrow kernel's, which has no partials), and partials grow with the rows
+        const int rows = max_C + max_B;
+        for (int m = 32; m < rows + 32; m += 32) gp = std::max(gp, plan_layer(ctx->cfg, std::min(m, rows)).partial_bytes());
         *bytes = layout(ctx->cfg, max_C, max_B).end_fixed + gp;
         return SLW_OK;
     });

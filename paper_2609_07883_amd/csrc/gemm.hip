@@ -1,33 +1,27 @@
-// bf16 GEMM out = A W^T on gfx950 matrix cores (v_mfma_f32_32x32x16_bf16).
+// bf16 GEMM out = A W^T on gfx950 matrix cores, with fused epilogues.
 //
-// A [m][k] and W [n][k] are both k-contiguous.  A work-group of four waves
-// computes a BM x BN tile; k advances in steps of 64 through a double-buffered
-// LDS tile (one barrier per step, next tile prefetched into registers while
-// the current one feeds the matrix cores).  LDS rows are 128 bytes; the
-// 16-byte chunk c of row r is stored at c ^ ((r >> 1) & 7) so that the rows
-// read by one MFMA operand load hit distinct banks.
+// A [m][k] and W [n][k] are both k-contiguous.  Two kernels:
+//   tile_kernel    BM x BN output tiles staged through LDS, for everything
+//                  but the smallest batches; k may be split across
+//                  work-groups, whose fp32 partial sums a second kernel adds
+//                  before it applies the same epilogue;
+//   narrow_kernel  weight streaming for a few rows, k split over the waves of
+//                  one work-group.
 //
-// Each wave's 64 columns are two 32-column MFMA tiles whose accumulators sit
-// in the same lanes at the same element index.  Two epilogues use that by
-// choosing which W rows feed the two tiles:
-//   SwiGLU: tile 0 takes gate rows, tile 1 the matching up rows, so a lane
-//           holds gate and up of one output and writes silu(gate) * up;
-//   QKV:    within each head, tile 0 takes dims i and tile 1 dims i + hd/2,
-//           so a lane holds both halves of a RoPE pair, rotates them, and
-//           writes q, or writes k and v straight into their KV pages.
-// Small problems split k across work-groups; fp32 partial sums are then
-// reduced by a second kernel that applies the same epilogue.
+// Two epilogues need two W rows of one output in the same lane: SwiGLU (a gate
+// row and its up row) and QKV (dims i and i + hd/2 of a head, a RoPE pair).
+// Both kernels choose which W rows feed which MFMA rows so that the two sit
+// in one lane at the same element of two accumulators.
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 #include "kernels.h"
 
 namespace slw {
 namespace {
-
-constexpr int BK_MAX = 64;  // k-steps per LDS stage are 32 or 64 wide
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
@@ -37,21 +31,6 @@ __device__ __forceinline__ int qkv_dim(int cw, int hd) {
     if (hd != 128) return cw;
     const int b = cw >> 5;
     return ((((b & 1) << 1) | (b >> 1)) << 5) | (cw & 31);
-}
-
-// W row feeding B column c (c = n0 + tile row).
-template <int EPI>
-__device__ __forceinline__ int w_row(const GemmArgs& g, int c) {
-    if (EPI == EPI_SWIGLU) {
-        const int sub = c >> 5, f = g.n >> 1;
-        const int col = (sub >> 1) * 32 + (c & 31);
-        return (sub & 1) ? f + col : col;
-    }
-    if (EPI == EPI_QKV) {
-        const int cw = c % g.hd;
-        return c - cw + qkv_dim(cw, g.hd);
-    }
-    return c;
 }
 
 // Rotate (x0, x1) = dims (d0, d0 + hd/2) of head hg of row `row` by
@@ -89,16 +68,6 @@ __device__ __forceinline__ void qkv_store(const GemmArgs& g, int row, int hg, in
     qkv_store_cs(g, row, hg, d0, x0, x1, cs, hg < g.hq ? 0 : g.slot[row]);
 }
 
-// LDS rows hold BK bf16 (BK/8 chunks of 16 bytes).  Chunk c of row r is
-// stored at c ^ ((r / (16 / CPR)) % CPR): the rows read by one MFMA operand
-// load land on distinct banks for both 128-byte (BK 64) and 64-byte (BK 32)
-// rows.
-template <int BK>
-__device__ __forceinline__ int swz(int row, int chunk) {
-    constexpr int CPR = BK / 8;
-    return chunk ^ ((row / (16 / CPR)) & (CPR - 1));
-}
-
 // Tile (tm, tn) at position t of the grouped tile order: group_m tile rows
 // at a time, column by column within a group, so that tiles that run
 // together share A rows and B columns.  With at most 16 tile rows a group
@@ -126,16 +95,23 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
-// Direct global->LDS load of 16 bytes per lane: lane l's bytes land at
-// lds + 16 l (lds is wave-uniform).  Issued as assembly so that the compiler,
-// which cannot tell which LDS buffer such a load writes, does not make every
-// later LDS read wait for all of them; the main loop waits for them itself.
-// M0 is a reserved register that the compiler sets right before each
-// instruction that reads it; no compiler-generated code in these kernels
-// uses it, so the value left there is never relied on.
-__device__ __forceinline__ void load_lds16(const void* src, void* lds) {
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)));
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(dst) : "memory");
+// Wait until at most N LDS operations of this wave are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() {
+    static_assert(N >= 0 && N < 16, "lgkmcnt range");
+    __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+}
+
+// Direct global->LDS load of 16 bytes per lane from base + off (base is
+// wave-uniform): lane l's bytes land at lds + 16 l (lds is wave-uniform).
+// Issued as assembly so that the compiler, which cannot tell which LDS buffer
+// such a load writes, does not make every later LDS read wait for all of
+// them; the main loop waits for them itself.  M0 is a reserved register that
+// the compiler sets right before each instruction that reads it; no
+// compiler-generated code in these kernels uses it, so the value left there
+// is never relied on.
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
 }
 
 // Workgroup barrier with no memory fence: the asm statement's memory clobber
@@ -143,530 +119,472 @@ __device__ __forceinline__ void load_lds16(const void* src, void* lds) {
 // waits it needs are issued explicitly before it.
 __device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" ::: "memory"); }
 
-// Main loops:
-//   RING == 0:   registers prefetch the next k step while the current one
-//                feeds the matrix cores, then write it to the second of two
-//                LDS buffers (one barrier per step).  The k-32 tiles of this
-//                kind ask for two waves per SIMD so that two work-groups fit
-//                on a CU.
-//   RING = 2..4: a ring of RING LDS buffers filled by direct global->LDS
-//                loads (16 bytes per lane) issued RING - 1 steps ahead; no
-//                staging registers.  Each lane loads the 16-byte chunk that
-//                belongs at its LDS slot, so the XOR layout is kept.  A counted
-//                wait for the wave's own loads of the step plus a bare barrier
-//                make every wave's loads visible; the same barrier proves that
-//                the buffer refilled next was finished by all waves.
-// Main loop of one tile: acc = A rows [m0, m0 + BM) times W rows
-// [n0, n0 + BN) over k steps [kb, kb + nk BK).  The register-staged loop ends
-// on a barrier; after a ring loop, callers that reuse the LDS buffers first
-// wait for every wave.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int RING, int EPI>
-__device__ __forceinline__ void tile_mainloop(const GemmArgs& g, int m0, int n0, int kb, int nk,
-                                              bf16 (*As)[BM * BK], bf16 (*Bs)[BN * BK],
-                                              f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32]) {
-    constexpr int THREADS = WAVES_M * WAVES_N * 64;
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int CPR = BK / 8;  // 16-byte chunks per LDS row
-    constexpr int A_LOADS = BM * CPR / THREADS;
-    constexpr int B_LOADS = BN * CPR / THREADS;
-    static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small");
-    static_assert(WN % 64 == 0, "paired epilogues need whole 64-column pairs per wave");
+// ---------------------------------------------------------------------------
+// Tile kernel.  Eight waves (WAVES_M x WAVES_N) compute a BM x BN tile with
+// 16 x 16 x 32 MFMAs, weights as the A operand; k advances 64 at a time
+// through two LDS buffers per operand.
+//
+// What bounds it: at the largest tile the chip runs into its power limit (the
+// same kernel on all-zero operands is 1.35 x faster), so the design saves
+// energy per product as much as it hides latency: 16 x 16 x 32 MFMAs touch
+// the accumulators half as often per product as 32 x 32 x 16 (+9% at 4096 x
+// 28672 x 4096), every operand byte is read from LDS once per k step, and no
+// register staging is used.
+//
+// Schedule.  A wave's tile is cut into four quadrants: its A rows in two
+// halves (A0, A1), its B columns in two halves.  A k step runs four phases,
+// one quadrant each, in the order A0 Bf, A0 Bs, A1 Bs, A1 Bf (first and second
+// B half swap roles every step), so that each half is read from LDS once per
+// step, one phase ahead of the MFMAs that need it:
+//   phase 0 reads Bs(t), phase 1 A1(t), phase 2 A0(t+1), phase 3 Bf(t+1).
+// A half's LDS region is free one phase after the phase that read it, and is
+// refilled then with the same half of step t + 2 by direct global->LDS loads
+// (phase 0 issues A0, phase 1 Bf, phase 2 Bs, phase 3 A1): each load has five
+// phases to land, where a ring of whole steps drained its queue once a step.
+// A phase ends on counted waits (this wave's reads of the phase before are
+// done; its loads of the half read next have landed) and a bare barrier that
+// makes both true for all waves.  LDS reads and loads are spread between the
+// MFMAs of a phase, in an order pinned by scheduling barriers: issued together
+// at its start, the loads of eight waves held up every wave's MFMAs (3-5%).
+//
+// Measured against the 256 x 256 two-buffer ring with 32 x 32 x 16 MFMAs that
+// it replaced (8B layer, three weight sets in turn): gate/up 470 -> 374 us at
+// 2080 rows (1040 -> 1306 TFLOP/s), 165 -> 98 at 512; down 286 -> 225 at
+// 2080; qkv 138 -> 86 at 2080; output 109 -> 69 at 2080.
+//
+// LDS rows hold 64 bf16 (128 bytes, one cache line per load); the 16-byte
+// chunk c of row r is stored at c ^ ((r >> 1) & 7), so that the rows read by
+// eight consecutive lanes hit distinct banks.
+//
+// Column order.  MFMA row 4 g + e of the wave's B tile j (lane group g,
+// element e of its result) takes the W row that gives a lane consecutive
+// output columns over its tiles: 8 HB of them (16 at BN 256), or for the
+// paired epilogues 4 HB outputs with both members of each pair, so every
+// epilogue access is 8 or 16 bytes wide.
+// ---------------------------------------------------------------------------
+template <int BM_, int BN_, int WAVES_M_, int WAVES_N_>
+struct Tile {
+    static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
+    static constexpr int NW = WAVES_M * WAVES_N, THREADS = NW * 64;
+    static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+    // 16-row tiles of a wave's A halves, 16-column tiles of each B half
+    static constexpr int HA = WM / 16, HA0 = (HA + 1) / 2, HA1 = HA - HA0, HB = WN / 32;
+    // 1 KB loads (8 LDS rows) that fill each half, and how many of them a wave
+    // issues; where the waves do not divide them, some piece is loaded twice
+    // (the same bytes to the same place), so that every wave counts the same
+    static constexpr int GA0 = WAVES_M * HA0 * 2, GA1 = WAVES_M * HA1 * 2, GB = WAVES_N * HB * 2;
+    static constexpr int LA0 = (GA0 + NW - 1) / NW, LA1 = (GA1 + NW - 1) / NW, LB = (GB + NW - 1) / NW;
+    static constexpr int LALL = LA0 + LA1 + 2 * LB;  // loads of a step
+    static constexpr int ABUF = BM * 128, BBUF = BN * 128, LDS = 2 * (ABUF + BBUF);
+    // two work-groups share a CU (four waves per SIMD, 128 registers) where LDS
+    // and registers allow it
+    static constexpr bool TWO = 2 * LDS <= 160 * 1024 && HA * 2 * HB * 4 + HA * 8 + HB * 16 <= 96;
+    static_assert(BM % (16 * WAVES_M) == 0 && BN % (32 * WAVES_N) == 0 && HA >= 2, "whole MFMA tiles in every half");
+    static_assert(LALL + LA0 + LB < 64, "vmcnt range");
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+// First W row of the lane's outputs and, for the paired epilogues, the row of
+// their partners: lane group g of wave column wn of the tile at column n0.
+template <int EPI, class T>
+__device__ __forceinline__ void lane_cols(const GemmArgs& g, int n0, int wn, int grp, int& c0, int& c1) {
+    if (EPI == EPI_SWIGLU) {
+        c0 = (n0 >> 1) + wn * (T::WN / 2) + grp * 4 * T::HB;
+        c1 = c0 + (g.n >> 1);
+    } else if (EPI == EPI_QKV) {
+        const int p = (n0 >> 1) + wn * (T::WN / 2) + grp * 4 * T::HB, half = g.hd >> 1;
+        c0 = (p / half) * g.hd + p % half;
+        c1 = c0 + half;
+    } else {
+        c0 = n0 + wn * T::WN + grp * 8 * T::HB;
+        c1 = c0 + 4 * T::HB;
+    }
+}
 
-    // Wave-uniform bases plus 32-bit per-lane element offsets (operands are
-    // below 2^31 elements).  Rows past m read row m-1 instead: they only feed
-    // output rows that are never stored, and an unconditional load keeps the
-    // prefetch asynchronous.
-    const bf16* A = static_cast<const bf16*>(g.a) + kb;
-    const bf16* W = static_cast<const bf16*>(g.w) + kb;
+// NV consecutive bf16 (4 or 8) at dst.
+template <int NV>
+__device__ __forceinline__ void store_bf16(bf16* dst, const bf16 (&v)[NV]) {
+    if constexpr (NV == 8)
+        *reinterpret_cast<bf16x8*>(dst) = bf16x8{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+    else
+        *reinterpret_cast<bf16x4*>(dst) = bf16x4{v[0], v[1], v[2], v[3]};
+}
 
+// Epilogue of a wave's tile.  acc[i][j]: row 16 i + lane % 16, B tile j (HB
+// tiles of the first half, then HB of the second), columns as in lane_cols.
+// Rows past m are not stored; their table and residual reads are clamped to
+// row m - 1.  Reads of a few row groups come before any of their stores: the
+// compiler cannot tell that the stores do not alias them, so interleaved
+// they would each wait out a memory round trip.
+template <class T, int EPI, bool SPLIT>
+__device__ __forceinline__ void tile_store(const GemmArgs& g, int m0, int n0, int wm, int wn, int lane,
+                                           float* __restrict__ partial, const f32x4 (&acc)[T::HA][2 * T::HB]) {
+    constexpr int HA = T::HA, HB = T::HB, NV = 4 * HB;
+    const int rbase = m0 + wm * T::WM + (lane & 15);
+    int c0, c1;
+    lane_cols<EPI, T>(g, n0, wn, lane >> 4, c0, c1);
+    if constexpr (SPLIT) {  // partial sums [m][n], W row order
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < HA; ++i) {
+            const int row = rbase + i * 16;
+            if (row >= g.m) continue;
+            float* p = partial + static_cast<size_t>(row) * g.n;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x16{};
-
-    int a_row[TM], b_row[TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) a_row[i] = wm * WM + i * 32 + (lane & 31);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) b_row[j] = wn * WN + j * 32 + (lane & 31);
-    const int kg = lane >> 5;
-
-    // Fragments of k-step s+1 are read from LDS while the MFMAs of step s run.
-    auto compute = [&](int buf) {
-        bf16x8 fa[2][TM], fb[2][TN];
-        auto read_frags = [&](int s, bf16x8* a, bf16x8* b) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                a[i] = *reinterpret_cast<const bf16x8*>(&As[buf][a_row[i] * BK + swz<BK>(a_row[i], 2 * s + kg) * 8]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                b[j] = *reinterpret_cast<const bf16x8*>(&Bs[buf][b_row[j] * BK + swz<BK>(b_row[j], 2 * s + kg) * 8]);
-        };
-        read_frags(0, fa[0], fb[0]);
-#pragma unroll
-        for (int s = 0; s < BK / 16; ++s) {
-            const int c = s & 1;
-            if (s + 1 < BK / 16) read_frags(s + 1, fa[c ^ 1], fb[c ^ 1]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fa[c][i], fb[c][j], acc[i][j]);
+            for (int j = 0; j < HB; ++j) {
+                *reinterpret_cast<f32x4*>(p + c0 + 4 * j) = acc[i][j];
+                *reinterpret_cast<f32x4*>(p + c1 + 4 * j) = acc[i][HB + j];
+            }
         }
-        // Instruction order for the scheduler: the first slice's reads, then
-        // per slice one next-slice read after each of the first TM + TN
-        // MFMAs.  Left alone, the compiler issues each slice's reads right
-        // before the MFMAs that use them and waits for them there (gate/up
-        // and down +4-5% with the interleave).
-        constexpr int NR = TM + TN, NM = TM * TN;
-        if constexpr (NM >= NR) {
-            __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);  // 0x100: LDS reads
+    } else if constexpr (EPI == EPI_SWIGLU) {
 #pragma unroll
-            for (int s = 0; s < BK / 16; ++s) {
-                if (s + 1 < BK / 16) {
+        for (int i = 0; i < HA; ++i) {
+            const int row = rbase + i * 16;
+            if (row >= g.m) continue;
+            bf16 o[NV];
 #pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);  // 0x8: MFMA
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    }
-                    if constexpr (NM > NR) __builtin_amdgcn_sched_group_barrier(0x8, NM - NR, 0);
+            for (int v = 0; v < NV; ++v) o[v] = f2bf(silu(acc[i][v / 4][v % 4]) * acc[i][HB + v / 4][v % 4]);
+            store_bf16<NV>(static_cast<bf16*>(g.out) + static_cast<size_t>(row) * g.ldo + c0, o);
+        }
+    } else if constexpr (EPI == EPI_QKV) {
+        const int half = g.hd >> 1, hg = c0 / g.hd, d0 = c0 % g.hd, d1 = d0 + half;
+        const bool rot = hg < g.hq + g.hkv, paged = hg >= g.hq;
+        constexpr int IC = 2;  // row groups whose tables are read at once
+#pragma unroll
+        for (int i0 = 0; i0 < HA; i0 += IC) {
+            f32x4 cs[IC][2 * HB];  // (cos, sin) of the lane's NV dims
+            int sl[IC];
+#pragma unroll
+            for (int i = 0; i < IC; ++i) {
+                const int row = min(rbase + (i0 + i) * 16, g.m - 1);
+                const f32x4* src = reinterpret_cast<const f32x4*>(g.rope_cs + static_cast<size_t>(row) * half + d0);
+#pragma unroll
+                for (int j = 0; j < 2 * HB; ++j) cs[i][j] = rot ? src[j] : f32x4{1.f, 0.f, 1.f, 0.f};
+                sl[i] = paged ? g.slot[row] : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < IC; ++i) {
+                const int row = rbase + (i0 + i) * 16;
+                if (i0 + i >= HA || row >= g.m) continue;
+                bf16 y0[NV], y1[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const float x0 = acc[i0 + i][v / 4][v % 4], x1 = acc[i0 + i][HB + v / 4][v % 4];
+                    const float co = cs[i][v / 2][2 * (v & 1)], si = cs[i][v / 2][2 * (v & 1) + 1];
+                    y0[v] = f2bf(rot ? x0 * co - x1 * si : x0);
+                    y1[v] = f2bf(rot ? x1 * co + x0 * si : x1);
+                }
+                bf16* out = static_cast<bf16*>(g.out) + static_cast<size_t>(row) * g.ldo;
+                store_bf16<NV>(out + c0, y0);
+                store_bf16<NV>(out + c1, y1);
+                if (!paged) continue;
+                const size_t blk = sl[i] >> 4, t = sl[i] & 15;
+                if (rot) {
+                    bf16* pg = static_cast<bf16*>(g.k_pool) + (blk * g.hkv + (hg - g.hq)) * g.hd * 16 + t * 32;
+                    store_bf16<NV>(pg + (d0 >> 5) * 512 + (d0 & 31), y0);
+                    store_bf16<NV>(pg + (d1 >> 5) * 512 + (d1 & 31), y1);
                 } else {
-                    __builtin_amdgcn_sched_group_barrier(0x8, NM, 0);
+                    // dim-major page: consecutive rows of a chunk are consecutive
+                    // tokens, so 16 lanes write one 32-byte row of the page
+                    bf16* pg = static_cast<bf16*>(g.v_pool) + (blk * g.hkv + (hg - g.hq - g.hkv)) * g.hd * 16 + t;
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        pg[(d0 + v) * 16] = y0[v];
+                        pg[(d1 + v) * 16] = y1[v];
+                    }
                 }
             }
         }
+    } else {
+        constexpr int IC = HA < 4 ? HA : 4;  // row groups whose residual is read at once
+#pragma unroll
+        for (int i0 = 0; i0 < HA; i0 += IC) {
+            f32x4 r[IC][2 * HB];
+#pragma unroll
+            for (int i = 0; i < IC; ++i) {
+                const size_t o = static_cast<size_t>(min(rbase + (i0 + i) * 16, g.m - 1)) * g.ldo + c0;
+#pragma unroll
+                for (int j = 0; j < 2 * HB; j += 2) {
+                    if constexpr (EPI == EPI_RESID_F32OUT) {
+                        const bf16x8 b = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(g.resid) + o + 4 * j);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) r[i][j + e / 4][e % 4] = bf2f(b[e]);
+                    } else {
+                        const f32x4* src = reinterpret_cast<const f32x4*>(static_cast<const float*>(g.resid) + o + 4 * j);
+                        r[i][j] = src[0];
+                        r[i][j + 1] = src[1];
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < IC; ++i) {
+                const int row = rbase + (i0 + i) * 16;
+                if (i0 + i >= HA || row >= g.m) continue;
+                const size_t o = static_cast<size_t>(row) * g.ldo + c0;
+#pragma unroll
+                for (int j = 0; j < 2 * HB; j += 2) {
+                    const f32x4 a = acc[i0 + i][j] + r[i][j], b = acc[i0 + i][j + 1] + r[i][j + 1];
+                    if constexpr (EPI == EPI_RESID_F32OUT) {
+                        f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(g.out) + o + 4 * j);
+                        dst[0] = a;
+                        dst[1] = b;
+                    } else {
+                        const bf16 v[8] = {f2bf(a[0]), f2bf(a[1]), f2bf(a[2]), f2bf(a[3]),
+                                           f2bf(b[0]), f2bf(b[1]), f2bf(b[2]), f2bf(b[3])};
+                        store_bf16<8>(static_cast<bf16*>(g.out) + o + 4 * j, v);
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Grid (tiles, splits); blockIdx.y takes k_per_split of the k range.
+template <class T, int EPI, bool SPLIT>
+__global__ __launch_bounds__(T::THREADS, T::TWO ? T::NW / 2 : T::NW / 4) void tile_kernel(GemmArgs g,
+                                                                                        float* __restrict__ partial,
+                                                                                        int k_per_split) {
+    constexpr int HA = T::HA, HA0 = T::HA0, HA1 = T::HA1, HB = T::HB, NW = T::NW, ABUF = T::ABUF, BBUF = T::BBUF;
+    constexpr int LA0 = T::LA0, LA1 = T::LA1, LB = T::LB, LALL = T::LALL;
+    constexpr int RA0 = HA0 * 2, RA1 = HA1 * 2, RB = HB * 2;  // LDS reads of each half per step
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    // A buffers of even and odd steps, then the B buffers
+    __shared__ __attribute__((aligned(1024))) char smem[T::LDS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int wm = wave / T::WAVES_N, wn = wave % T::WAVES_N;
+    int tm, tn;
+    tile_of(blockIdx.x, (g.m + T::BM - 1) / T::BM, g.n / T::BN, tm, tn);
+    const int m0 = tm * T::BM, n0 = tn * T::BN;
+    const int nk = k_per_split / 64;
+    const uint32_t lds0 =
+        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&smem[0])));
+
+    // Loads: lane l brings chunk (l % 8) ^ swizzle of row l / 8 of its piece.
+    // Wave-uniform 64-bit bases (one per B half: a pair's rows may be far
+    // apart) plus 32-bit lane offsets within the tile's rows.  Rows past m
+    // read row m - 1: they only feed output rows that are never stored.
+    const size_t k0 = static_cast<size_t>(blockIdx.y) * k_per_split;
+    const char* Ab = static_cast<const char*>(g.a) + (static_cast<size_t>(m0) * g.lda + k0) * 2;
+    int c00, c01;
+    lane_cols<EPI, T>(g, n0, 0, 0, c00, c01);
+    const char* Wb[2];
+    Wb[0] = static_cast<const char*>(g.w) + (static_cast<size_t>(c00) * g.k + k0) * 2;
+    Wb[1] = static_cast<const char*>(g.w) + (static_cast<size_t>(c01) * g.k + k0) * 2;
+    uint32_t oA0[LA0], oA1[LA1], oB[2][LB], dA0[LA0], dA1[LA1], dB[2][LB];
+    const int r_in = lane >> 3;
+    auto chunk = [&](int row) { return ((lane & 7) ^ ((row >> 1) & 7)) * 16; };
+    auto set_a = [&](int tiles, int first, int pieces, int i, uint32_t& off, uint32_t& dst) {
+        const int piece = (wave + i * NW) % pieces, per = tiles * 2;
+        const int r0 = (piece / per) * T::WM + first * 16 + (piece % per) * 8, row = r0 + r_in;
+        off = static_cast<uint32_t>(min(row, g.m - 1 - m0)) * static_cast<uint32_t>(g.lda * 2) + chunk(row);
+        dst = lds0 + r0 * 128;
+    };
+    auto set_b = [&](int h, int i) {
+        const int piece = (wave + i * NW) % T::GB, w = piece / (HB * 2), p0 = (piece % (HB * 2)) * 8;
+        const int r0 = w * T::WN + h * HB * 16 + p0, rh = p0 + r_in;  // first LDS row; row in the half
+        int a0, a1;  // rh = 16 j + 4 grp + e
+        lane_cols<EPI, T>(g, n0, w, (rh >> 2) & 3, a0, a1);
+        const int wrow = (h ? a1 - c01 : a0 - c00) + 4 * (rh >> 4) + (rh & 3);
+        oB[h][i] = static_cast<uint32_t>(wrow) * static_cast<uint32_t>(g.k * 2) + chunk(r0 + r_in);
+        dB[h][i] = lds0 + 2 * ABUF + r0 * 128;
+    };
+#pragma unroll
+    for (int i = 0; i < LA0; ++i) set_a(HA0, 0, T::GA0, i, oA0[i], dA0[i]);
+#pragma unroll
+    for (int i = 0; i < LA1; ++i) set_a(HA1, HA0, T::GA1, i, oA1[i], dA1[i]);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        set_b(0, i);
+        set_b(1, i);
+    }
+    auto ldA0 = [&](int x, int t, int par) { load_lds16(Ab + static_cast<size_t>(t) * 128, oA0[x], dA0[x] + par * ABUF); };
+    auto ldA1 = [&](int x, int t, int par) { load_lds16(Ab + static_cast<size_t>(t) * 128, oA1[x], dA1[x] + par * ABUF); };
+    auto ldB = [&](int h, int x, int t, int par) {
+        load_lds16(Wb[h] + static_cast<size_t>(t) * 128, oB[h][x], dB[h][x] + par * BBUF);
     };
 
-    if constexpr (RING == 0) {
-        int a_off[A_LOADS], a_lds[A_LOADS];
+    // LDS reads: slice s (32 of the step's 64 k), chunk 4 s + lane / 16 of row lane % 16
+    const char* aF[2];
+    const char* bF[2];
 #pragma unroll
-        for (int i = 0; i < A_LOADS; ++i) {
-            const int idx = tid + i * THREADS, row = idx / CPR, ch = idx % CPR;
-            a_off[i] = min(m0 + row, g.m - 1) * g.lda + ch * 8;
-            a_lds[i] = row * BK + swz<BK>(row, ch) * 8;
+    for (int s = 0; s < 2; ++s) {
+        const int r = lane & 15, at = ((4 * s + (lane >> 4)) ^ ((r >> 1) & 7)) << 4;
+        aF[s] = smem + (wm * T::WM + r) * 128 + at;
+        bF[s] = smem + 2 * ABUF + (wn * T::WN + r) * 128 + at;
+    }
+    bf16x8 fa0[HA0][2], fa1[HA1][2], fb[2][HB][2];
+    f32x4 acc[HA][2 * HB];
+#pragma unroll
+    for (int i = 0; i < HA; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * HB; ++j) acc[i][j] = f32x4{};
+    auto rA0 = [&](int x, int par) {
+        fa0[x % HA0][x / HA0] = *reinterpret_cast<const bf16x8*>(aF[x / HA0] + par * ABUF + (x % HA0) * 2048);
+    };
+    auto rA1 = [&](int x, int par) {
+        fa1[x % HA1][x / HA1] = *reinterpret_cast<const bf16x8*>(aF[x / HA1] + par * ABUF + (HA0 + x % HA1) * 2048);
+    };
+    auto rB = [&](auto h_c, int x, int par) {
+        constexpr int h = decltype(h_c)::value;
+        fb[h][x % HB][x / HB] = *reinterpret_cast<const bf16x8*>(bF[x / HB] + par * BBUF + (h * HB + x % HB) * 2048);
+    };
+    // MFMA x of quadrant (A half, B half), slice by slice
+    auto mma = [&](auto ah_c, auto bh_c, int x) {
+        constexpr int ah = decltype(ah_c)::value, bh = decltype(bh_c)::value, per = (ah ? HA1 : HA0) * HB;
+        const int s = x / per, i = (x % per) / HB, j = x % HB;
+        if constexpr (ah) acc[HA0 + i][bh * HB + j] = mfma16(fb[bh][j][s], fa1[i][s], acc[HA0 + i][bh * HB + j]);
+        else acc[i][bh * HB + j] = mfma16(fb[bh][j][s], fa0[i][s], acc[i][bh * HB + j]);
+    };
+    // The MFMAs of a quadrant with NR LDS reads and NL loads spread between them.
+    auto quadrant = [&](auto ah, auto bh, auto nr_c, auto nl_c, auto rd, auto ld) {
+        constexpr int NM = (decltype(ah)::value ? HA1 : HA0) * HB * 2, NR = decltype(nr_c)::value, NL = decltype(nl_c)::value;
+#pragma unroll
+        for (int x = 0; x < NM; ++x) {
+            constexpr int MAX = 16;
+#pragma unroll
+            for (int r = 0; r < MAX; ++r)
+                if (r < NR && r >= (NR * x + NM - 1) / NM && r < (NR * (x + 1) + NM - 1) / NM) rd(r);
+            mma(ah, bh, x);
+#pragma unroll
+            for (int l = 0; l < MAX; ++l)
+                if (l < NL && l >= (NL * x + NM - 1) / NM && l < (NL * (x + 1) + NM - 1) / NM) ld(l);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        int b_off[B_LOADS], b_lds[B_LOADS];
+    };
+    // End of a phase: at most NLDS of this wave's LDS reads (those of this phase)
+    // and NV of its loads (those younger than the half read next) are left.
+    auto phase_end = [&](auto nv_c, auto nlds_c) {
+        wait_lgkmcnt<decltype(nlds_c)::value>();
+        wait_vmcnt<decltype(nv_c)::value>();
+        barrier_only();
+    };
+    // One k step of parity PAR (its buffers, and the B half that comes first).
+    // MODE 0: loads of step t + 2 are issued; 1: the step before the last; 2: the last.
+    auto step = [&](auto par_c, auto mode_c, int t) {
+        constexpr int PAR = decltype(par_c)::value, MODE = decltype(mode_c)::value;
+        constexpr bool L = MODE == 0, R = MODE != 2;
+        using F = std::integral_constant<int, PAR>;
+        using S = std::integral_constant<int, 1 - PAR>;
+        quadrant(I0{}, F{}, std::integral_constant<int, RB>{}, std::integral_constant<int, L ? LA0 : 0>{},
+                 [&](int x) { rB(S{}, x, PAR); }, [&](int x) { ldA0(x, t + 2, PAR); });
+        phase_end(std::integral_constant<int, L ? LALL + LA0 : R ? LALL : 0>{}, std::integral_constant<int, RB>{});
+        quadrant(I0{}, S{}, std::integral_constant<int, RA1>{}, std::integral_constant<int, L ? LB : 0>{},
+                 [&](int x) { rA1(x, PAR); }, [&](int x) { ldB(PAR, x, t + 2, PAR); });
+        phase_end(std::integral_constant<int, L ? LALL + LB : R ? LALL - LA0 : 0>{}, std::integral_constant<int, RA1>{});
+        quadrant(I1{}, S{}, std::integral_constant<int, R ? RA0 : 0>{}, std::integral_constant<int, L ? LB : 0>{},
+                 [&](int x) { rA0(x, 1 - PAR); }, [&](int x) { ldB(1 - PAR, x, t + 2, PAR); });
+        if (R) phase_end(std::integral_constant<int, L ? LALL + LB : LB + LA1>{}, std::integral_constant<int, RA0>{});
+        quadrant(I1{}, F{}, std::integral_constant<int, R ? RB : 0>{}, std::integral_constant<int, L ? LA1 : 0>{},
+                 [&](int x) { rB(S{}, x, 1 - PAR); }, [&](int x) { ldA1(x, t + 2, PAR); });
+        if (R) phase_end(std::integral_constant<int, L ? LALL + LA1 : LA1>{}, std::integral_constant<int, RB>{});
+    };
+    // Loads of the first two steps, in the order the phases read them; the
+    // first halves of step 0 are read here.  (A range of one step loads it twice.)
+    auto prologue = [&](auto p_c) {
+        constexpr int P = decltype(p_c)::value;
+        auto whole = [&](int t, int par) {
 #pragma unroll
-        for (int i = 0; i < B_LOADS; ++i) {
-            const int idx = tid + i * THREADS, row = idx / CPR, ch = idx % CPR;
-            b_off[i] = w_row<EPI>(g, n0 + row) * g.k + ch * 8;
-            b_lds[i] = row * BK + swz<BK>(row, ch) * 8;
-        }
-        bf16x8 ra[A_LOADS], rb[B_LOADS];
-        auto load_tile = [&](int kt) {
-            const bf16* Ak = A + kt * BK;
-            const bf16* Wk = W + kt * BK;
+            for (int x = 0; x < LA0; ++x) ldA0(x, t, par);
 #pragma unroll
-            for (int i = 0; i < A_LOADS; ++i) ra[i] = *reinterpret_cast<const bf16x8*>(Ak + a_off[i]);
+            for (int x = 0; x < LB; ++x) ldB(par, x, t, par);
 #pragma unroll
-            for (int i = 0; i < B_LOADS; ++i) rb[i] = *reinterpret_cast<const bf16x8*>(Wk + b_off[i]);
+            for (int x = 0; x < LB; ++x) ldB(1 - par, x, t, par);
+#pragma unroll
+            for (int x = 0; x < LA1; ++x) ldA1(x, t, par);
         };
-        auto store_tile = [&](int buf) {
+        whole(0, P);
+        whole(min(1, nk - 1), 1 - P);
+        wait_vmcnt<LALL + LA1>();
+        barrier_only();
 #pragma unroll
-            for (int i = 0; i < A_LOADS; ++i) *reinterpret_cast<bf16x8*>(&As[buf][a_lds[i]]) = ra[i];
+        for (int x = 0; x < RA0; ++x) rA0(x, P);
 #pragma unroll
-            for (int i = 0; i < B_LOADS; ++i) *reinterpret_cast<bf16x8*>(&Bs[buf][b_lds[i]]) = rb[i];
-        };
-        load_tile(0);
-        store_tile(0);
-        __syncthreads();
-        for (int kt = 0; kt < nk; ++kt) {
-            const int buf = kt & 1;
-            if (kt + 1 < nk) load_tile(kt + 1);
-            compute(buf);
-            if (kt + 1 < nk) store_tile(buf ^ 1);
-            __syncthreads();
+        for (int x = 0; x < RB; ++x) rB(std::integral_constant<int, P>{}, x, P);
+        wait_lgkmcnt<0>();
+        barrier_only();
+    };
+    // The last step has parity 1.
+    int t = 0;
+    if (nk & 1) {
+        prologue(I1{});
+        if (nk > 1) {
+            step(I1{}, I0{}, 0);
+            t = 1;
         }
     } else {
-        // One direct load fills 1 KB of LDS: RPI rows of BK values.  Wave w
-        // issues A loads w, w + NW, ... and B loads likewise.
-        constexpr int NW = WAVES_M * WAVES_N;
-        constexpr int RPI = 64 / CPR;
-        constexpr int A_INS = BM / RPI / NW, B_INS = BN / RPI / NW;
-        constexpr int PER_STEP = A_INS + B_INS;
-        static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "direct loads must split evenly");
-        static_assert(RING >= 2 && RING <= 4, "the counted waits cover rings of two to four buffers");
-        const int r_in = lane / CPR, stored = lane % CPR;
-        const bf16* a_src[A_INS];
-        int a_dst[A_INS];
-#pragma unroll
-        for (int i = 0; i < A_INS; ++i) {
-            const int row = (wave + i * NW) * RPI + r_in;
-            const int ch = stored ^ ((row / (16 / CPR)) & (CPR - 1));  // logical chunk stored at this slot
-            a_src[i] = A + static_cast<size_t>(min(m0 + row, g.m - 1)) * g.lda + ch * 8;
-            a_dst[i] = (wave + i * NW) * RPI * BK;
+        prologue(I0{});
+    }
+    if (nk > 1) {
+        for (; t + 2 < nk; t += 2) {
+            step(I0{}, I0{}, t);
+            step(I1{}, I0{}, t + 1);
         }
-        const bf16* b_src[B_INS];
-        int b_dst[B_INS];
-#pragma unroll
-        for (int i = 0; i < B_INS; ++i) {
-            const int row = (wave + i * NW) * RPI + r_in;
-            const int ch = stored ^ ((row / (16 / CPR)) & (CPR - 1));
-            b_src[i] = W + static_cast<size_t>(w_row<EPI>(g, n0 + row)) * g.k + ch * 8;
-            b_dst[i] = (wave + i * NW) * RPI * BK;
-        }
-        auto issue = [&](int kt) {
-            const int buf = kt % RING;
-#pragma unroll
-            for (int i = 0; i < A_INS; ++i)
-                load_lds16(a_src[i] + kt * BK, &As[buf][a_dst[i]]);
-#pragma unroll
-            for (int i = 0; i < B_INS; ++i)
-                load_lds16(b_src[i] + kt * BK, &Bs[buf][b_dst[i]]);
-        };
-#pragma unroll
-        for (int s = 0; s < RING - 1; ++s)
-            if (s < nk) issue(s);
-        for (int kt = 0; kt < nk; ++kt) {
-            // this wave's loads of step kt are done once at most the younger
-            // steps' loads (up to RING - 2 of them) are outstanding
-            const int younger = min(nk - 1 - kt, RING - 2);
-            if (RING >= 4 && younger >= 2) wait_vmcnt<2 * PER_STEP>();
-            else if (RING >= 3 && younger >= 1) wait_vmcnt<PER_STEP>();
-            else wait_vmcnt<0>();
-            barrier_only();
-            if (kt + RING - 1 < nk) issue(kt + RING - 1);
-            compute(kt % RING);
-        }
+        step(I0{}, I1{}, t);
     }
+    step(I1{}, I2{}, nk - 1);
+    tile_store<T, EPI, SPLIT>(g, m0, n0, wm, wn, lane,
+                              SPLIT ? partial + static_cast<size_t>(blockIdx.y) * g.m * g.n : nullptr, acc);
 }
 
-// Fused epilogue of one tile: element e of MFMA tile (i, j) of a wave is row
-// m0 + wm WM + 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4, B column
-// n0 + wn WN + 32 j + lane % 32.  The epilogue's inputs (RoPE table,
-// residual) are read for a whole block of rows before any of its stores:
-// the compiler cannot tell that the stores do not alias them, so reads and
-// stores interleaved per element would each wait out a memory round trip.
-// Reads of rows past m are clamped to row m - 1 and their stores skipped.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
-__device__ __forceinline__ void tile_store(const GemmArgs& g, int m0, int n0,
-                                           const f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32]) {
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int rbase = m0 + wm * WM + 4 * (lane >> 5);
-    const int cbase = n0 + wn * WN + (lane & 31);
-    if (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-        bf16* out = static_cast<bf16*>(g.out);
-#pragma unroll
-        for (int pr = 0; pr < TN / 2; ++pr) {
-            const int c0 = n0 + wn * WN + pr * 64;  // first B column of the pair (tile 2pr)
-            int hg = 0, d0 = 0, fcol = 0;
-            if (EPI == EPI_QKV) {
-                hg = c0 / g.hd;
-                d0 = ((c0 % g.hd) / 64) * 32 + (lane & 31);
-            } else {
-                fcol = (c0 >> 1) + (lane & 31);
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                float2 cs[16];
-                int sl[16];
-                if (EPI == EPI_QKV) {
-                    const bool rot = hg < g.hq + g.hkv, paged = hg >= g.hq;
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int row = min(rbase + i * 32 + 8 * (e >> 2) + (e & 3), g.m - 1);
-                        cs[e] = rot ? g.rope_cs[row * (g.hd / 2) + d0] : make_float2(1.f, 0.f);
-                        sl[e] = paged ? g.slot[row] : 0;
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-                    if (row >= g.m) continue;
-                    const float x0 = acc[i][2 * pr][e], x1 = acc[i][2 * pr + 1][e];
-                    if (EPI == EPI_QKV) qkv_store_cs(g, row, hg, d0, x0, x1, cs[e], sl[e]);
-                    else out[static_cast<size_t>(row) * g.ldo + fcol] = f2bf(silu(x0) * x1);
-                }
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        float r[TN][16];
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = min(rbase + i * 32 + 8 * (e >> 2) + (e & 3), g.m - 1);
-                const size_t o = static_cast<size_t>(row) * g.ldo + cbase + j * 32;
-                r[j][e] = EPI == EPI_RESID_F32OUT ? bf2f(static_cast<const bf16*>(g.resid)[o])
-                                                  : static_cast<const float*>(g.resid)[o];
-            }
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-                if (row >= g.m) continue;
-                const size_t o = static_cast<size_t>(row) * g.ldo + cbase + j * 32;
-                if (EPI == EPI_RESID_F32OUT)
-                    static_cast<float*>(g.out)[o] = acc[i][j][e] + r[j][e];
-                else
-                    static_cast<bf16*>(g.out)[o] = f2bf(acc[i][j][e] + r[j][e]);
-            }
-    }
-}
-
-// Split-K partial of one tile into P [m][n] (B column order).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
-__device__ __forceinline__ void tile_store_split(const GemmArgs& g, int m0, int n0, float* __restrict__ P,
-                                       const f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32]) {
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int rbase = m0 + wm * WM + 4 * (lane >> 5);
-    const int cbase = n0 + wn * WN + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-                if (row < g.m) P[static_cast<size_t>(row) * g.n + cbase + j * 32] = acc[i][j][e];
-            }
-}
-
-// Stream-K partial of one tile into P [BM][BN] (tile rows, B column order).
-template <int BM, int BN, int WAVES_M, int WAVES_N>
-__device__ __forceinline__ void tile_store_partial(float* __restrict__ P,
-                                                   const f32x16 (&acc)[BM / WAVES_M / 32][BN / WAVES_N / 32]) {
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int rbase = wm * WM + 4 * (lane >> 5);
-    const int cbase = wn * WN + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                P[(rbase + i * 32 + 8 * (e >> 2) + (e & 3)) * BN + cbase + j * 32] = acc[i][j][e];
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int RING, int EPI, bool SPLIT>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, (BK == 32 && RING == 0) ? 2 : 1) void gemm_kernel(
-    GemmArgs g, float* __restrict__ partial, int k_per_split) {
-    constexpr int NBUF = RING == 0 ? 2 : RING;
-    __shared__ __attribute__((aligned(16))) bf16 As[NBUF][BM * BK];
-    __shared__ __attribute__((aligned(16))) bf16 Bs[NBUF][BN * BK];
-    int tm, tn;
-    tile_of(blockIdx.x, (g.m + BM - 1) / BM, g.n / BN, tm, tn);
-    f32x16 acc[BM / WAVES_M / 32][BN / WAVES_N / 32];
-    tile_mainloop<BM, BN, WAVES_M, WAVES_N, BK, RING, EPI>(g, tm * BM, tn * BN, blockIdx.y * k_per_split,
-                                                          k_per_split / BK, As, Bs, acc);
-    if (SPLIT)
-        tile_store_split<BM, BN, WAVES_M, WAVES_N, EPI>(
-            g, tm * BM, tn * BN, partial + static_cast<size_t>(blockIdx.y) * g.m * g.n, acc);
-    else
-        tile_store<BM, BN, WAVES_M, WAVES_N, EPI>(g, tm * BM, tn * BN, acc);
-}
-
-// Stream-K schedule: whole tiles first, then equal shares of k steps.
-// Blocks [0, dp_tiles) each run one whole tile of the first dp_tiles of the
-// tile order.  The k steps of the remaining tiles, laid end to end (`iters`
-// of them), are cut into `workers` equal ranges, worker w taking
-// [w iters / workers, (w + 1) iters / workers).  A range covers the tail of
-// one tile, whole tiles and the head of another; whole tiles get the fused
-// epilogue, pieces are stored as partials in slot 2w (the range's first
-// piece) or 2w + 1 (its last) and summed by sk_fixup_kernel.  No block waits
-// for another.
-__device__ __forceinline__ int64_t sk_range_start(int w, int64_t iters, int workers) {
-    return static_cast<int64_t>(w) * iters / workers;
-}
-// Worker whose range holds step x: the largest w with w iters / workers <= x.
-__device__ __forceinline__ int sk_worker_of(int64_t x, int64_t iters, int workers) {
-    return static_cast<int>(((x + 1) * workers - 1) / iters);
-}
-
-// One piece of a stream-K range: k steps [k0, k1) of tile t, stored whole or
-// as the partial in `slot`.  Kept out of line: inlined into the loop over a
-// range's pieces, the tile code spills its accumulators.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int RING, int EPI>
-__device__ __noinline__ void sk_piece(const GemmArgs& g, float* __restrict__ partial, int t, int k0, int k1, int slot) {
-    constexpr int NBUF = RING == 0 ? 2 : RING;
-    __shared__ __attribute__((aligned(16))) bf16 As[NBUF][BM * BK];
-    __shared__ __attribute__((aligned(16))) bf16 Bs[NBUF][BN * BK];
-    const int nt_m = (g.m + BM - 1) / BM, nt_n = g.n / BN;
-    const int nk = g.k / BK;
-    f32x16 acc[BM / WAVES_M / 32][BN / WAVES_N / 32];
-    int tm, tn;
-    tile_coords(t, nt_m, nt_n, tm, tn);
-    tile_mainloop<BM, BN, WAVES_M, WAVES_N, BK, RING, EPI>(g, tm * BM, tn * BN, k0 * BK, k1 - k0, As, Bs, acc);
-    if (k0 == 0 && k1 == nk)
-        tile_store<BM, BN, WAVES_M, WAVES_N, EPI>(g, tm * BM, tn * BN, acc);
-    else
-        tile_store_partial<BM, BN, WAVES_M, WAVES_N>(partial + static_cast<size_t>(slot) * BM * BN, acc);
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int RING, int EPI>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, (BK == 32 && RING == 0) ? 2 : 1) void gemm_sk_kernel(
-    GemmArgs g, float* __restrict__ partial, int dp_tiles, int workers) {
-    const int nt_m = (g.m + BM - 1) / BM, nt_n = g.n / BN;
-    const int nk = g.k / BK;
-    // Steps of all tiles in one space, the whole tiles first: a whole-tile
-    // block's range is its tile, worker w's range follows dp_tiles * nk.
-    const int bid = blockIdx.x;
-    const int64_t iters = static_cast<int64_t>(nt_m * nt_n - dp_tiles) * nk;
-    int w = 0;
-    int64_t lo, hi;
-    if (bid < dp_tiles) {
-        lo = static_cast<int64_t>(xcd_order(bid, dp_tiles)) * nk;
-        hi = lo + nk;
-    } else {
-        // workers on one XCD take consecutive ranges (dp_tiles is a multiple of 8)
-        w = xcd_order(bid - dp_tiles, workers);
-        lo = static_cast<int64_t>(dp_tiles) * nk + sk_range_start(w, iters, workers);
-        hi = static_cast<int64_t>(dp_tiles) * nk + sk_range_start(w + 1, iters, workers);
-    }
-    for (int64_t it = lo; it < hi;) {
-        const int t = static_cast<int>(it / nk);
-        const int k0 = static_cast<int>(it - static_cast<int64_t>(t) * nk);
-        const int k1 = static_cast<int>(min<int64_t>(nk, k0 + (hi - it)));
-        if (it != lo) __syncthreads();  // every wave is done with the previous piece's LDS buffers
-        sk_piece<BM, BN, WAVES_M, WAVES_N, BK, RING, EPI>(g, partial, t, k0, k1, 2 * w + (it == lo ? 0 : 1));
-        it += k1 - k0;
-    }
-}
-
-// Sum the partial pieces of each stream-K tile that several workers shared
-// and apply the epilogue.  Block (x, y): tile dp_tiles + x of the order,
-// y-th group of 256 output units (a RoPE pair, or four outputs).
-template <int BM, int BN, int BK, int EPI>
-__global__ __launch_bounds__(256) void sk_fixup_kernel(GemmArgs g, const float* __restrict__ partial, int dp_tiles,
-                                                       int workers) {
-    const int nt_m = (g.m + BM - 1) / BM, nt_n = g.n / BN;
-    const int nk = g.k / BK;
-    const int64_t iters = static_cast<int64_t>(nt_m * nt_n - dp_tiles) * nk;
-    const int t = blockIdx.x;
-    const int64_t t0 = static_cast<int64_t>(t) * nk;
-    const int wa = sk_worker_of(t0, iters, workers), wb = sk_worker_of(t0 + nk - 1, iters, workers);
-    if (wa == wb) return;  // one worker ran the whole tile and stored it
-    int tm, tn;
-    tile_coords(dp_tiles + t, nt_m, nt_n, tm, tn);
-    const int m0 = tm * BM, n0 = tn * BN;
-    // slot of worker w's piece of this tile: its first piece unless its range starts before the tile
-    auto slot_of = [&](int w) { return 2 * w + (sk_range_start(w, iters, workers) < t0 ? 1 : 0); };
-    const int u = blockIdx.y * 256 + threadIdx.x;
-    if (EPI == EPI_QKV) {  // one unit per RoPE pair
-        const int half = g.hd / 2, pairs = BN / 2;
-        if (u >= BM * pairs) return;
-        const int r = u / pairs, j = u % pairs;
-        if (m0 + r >= g.m) return;
-        const int hl = j / half, d0 = j % half;
-        const int c0 = hl * g.hd + qkv_dim(d0, g.hd), c1 = hl * g.hd + qkv_dim(d0 + half, g.hd);
-        float x0 = 0.f, x1 = 0.f;
-        for (int w = wa; w <= wb; ++w) {
-            const float* P = partial + static_cast<size_t>(slot_of(w)) * BM * BN + r * BN;
-            x0 += P[c0];
-            x1 += P[c1];
-        }
-        qkv_store(g, m0 + r, n0 / g.hd + hl, d0, x0, x1);
-        return;
-    }
-    const int n_out = EPI == EPI_SWIGLU ? BN / 2 : BN;
-    const int per_row = n_out / 4;
-    if (u >= BM * per_row) return;
-    const int r = u / per_row, c4 = (u % per_row) * 4;
-    if (m0 + r >= g.m) return;
-    if (EPI == EPI_SWIGLU) {
-        const int gc = (c4 >> 5) * 64 + (c4 & 31);  // gate column in B order; up is +32
-        f32x4 gs = {}, us = {};
-        for (int w = wa; w <= wb; ++w) {
-            const float* P = partial + static_cast<size_t>(slot_of(w)) * BM * BN + r * BN + gc;
-            gs += *reinterpret_cast<const f32x4*>(P);
-            us += *reinterpret_cast<const f32x4*>(P + 32);
-        }
-        bf16* out = static_cast<bf16*>(g.out) + static_cast<size_t>(m0 + r) * g.ldo + n0 / 2 + c4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = f2bf(silu(gs[e]) * us[e]);
-        return;
-    }
-    f32x4 sum = {};
-    for (int w = wa; w <= wb; ++w)
-        sum += *reinterpret_cast<const f32x4*>(partial + static_cast<size_t>(slot_of(w)) * BM * BN + r * BN + c4);
-    const size_t o = static_cast<size_t>(m0 + r) * g.ldo + n0 + c4;
-    if (EPI == EPI_RESID_F32OUT) {
-        const bf16* rs = static_cast<const bf16*>(g.resid) + o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] += bf2f(rs[e]);
-        *reinterpret_cast<f32x4*>(static_cast<float*>(g.out) + o) = sum;
-    } else {
-        sum += *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.resid) + o);
-        bf16* out = static_cast<bf16*>(g.out) + o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = f2bf(sum[e]);
-    }
-}
-
-// Sum split-K partials [splits][m][n] (B column order) and apply the epilogue.
+// Sum split-K partials [splits][m][n] (W row order) and apply the epilogue:
+// four outputs (or pairs) per thread.
 template <int EPI>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const float* __restrict__ part,
-                                                            int splits) {
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const float* __restrict__ part, int splits) {
+    constexpr bool PAIR = EPI == EPI_QKV || EPI == EPI_SWIGLU;
     const size_t slab = static_cast<size_t>(g.m) * g.n;
     const size_t idx = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-    if (EPI == EPI_QKV) {  // one thread per RoPE pair
-        const int pairs = g.n / 2, half = g.hd / 2;
-        if (idx >= static_cast<size_t>(g.m) * pairs) return;
-        const int row = static_cast<int>(idx / pairs), j = static_cast<int>(idx % pairs);
-        const int hg = j / half, d0 = j % half;
-        const size_t c0 = static_cast<size_t>(hg) * g.hd + qkv_dim(d0, g.hd);
-        const size_t c1 = static_cast<size_t>(hg) * g.hd + qkv_dim(d0 + half, g.hd);
-        float x0 = 0.f, x1 = 0.f;
-        for (int z = 0; z < splits; ++z) {
-            const float* p = part + z * slab + static_cast<size_t>(row) * g.n;
-            x0 += p[c0];
-            x1 += p[c1];
-        }
-        qkv_store(g, row, hg, d0, x0, x1);
-        return;
-    }
-    const int n_out = (EPI == EPI_SWIGLU) ? g.n / 2 : g.n;
-    const int per_row = n_out / 4;
+    const int per_row = (PAIR ? g.n / 2 : g.n) / 4;
     if (idx >= static_cast<size_t>(g.m) * per_row) return;
-    const int row = static_cast<int>(idx / per_row);
-    const int c4 = static_cast<int>(idx % per_row) * 4;
-    const size_t o = static_cast<size_t>(row) * g.ldo + c4;
-    if (EPI == EPI_SWIGLU) {
-        const int gc = (c4 >> 5) * 64 + (c4 & 31);  // gate column in B order; up is +32
-        f32x4 gs = {}, us = {};
-        for (int z = 0; z < splits; ++z) {
-            const float* p = part + z * slab + static_cast<size_t>(row) * g.n + gc;
-            gs += *reinterpret_cast<const f32x4*>(p);
-            us += *reinterpret_cast<const f32x4*>(p + 32);
-        }
-        bf16* out = static_cast<bf16*>(g.out) + o;
+    const int row = static_cast<int>(idx / per_row), c = static_cast<int>(idx % per_row) * 4;
+    const int half = g.hd >> 1;
+    int c0 = c, c1 = 0;  // W rows of the four outputs and of their partners
+    if (EPI == EPI_SWIGLU) c1 = c + (g.n >> 1);
+    if (EPI == EPI_QKV) {
+        c0 = (c / half) * g.hd + c % half;
+        c1 = c0 + half;
+    }
+    const float* p = part + static_cast<size_t>(row) * g.n;
+    f32x4 a = {}, b = {};
+    for (int z = 0; z < splits; ++z) {
+        a += *reinterpret_cast<const f32x4*>(p + z * slab + c0);
+        if (PAIR) b += *reinterpret_cast<const f32x4*>(p + z * slab + c1);
+    }
+    if constexpr (EPI == EPI_QKV) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = f2bf(silu(gs[e]) * us[e]);
+        for (int e = 0; e < 4; ++e) qkv_store(g, row, c / half, c % half + e, a[e], b[e]);
         return;
     }
-    f32x4 s = {};
-    for (int z = 0; z < splits; ++z)
-        s += *reinterpret_cast<const f32x4*>(part + z * slab + static_cast<size_t>(row) * g.n + c4);
-    if (EPI == EPI_RESID_F32OUT) {
-        const bf16* r = static_cast<const bf16*>(g.resid) + o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] += bf2f(r[e]);
-        *reinterpret_cast<f32x4*>(static_cast<float*>(g.out) + o) = s;
-    } else {
-        s += *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.resid) + o);
-        bf16* out = static_cast<bf16*>(g.out) + o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = f2bf(s[e]);
+    const size_t o = static_cast<size_t>(row) * g.ldo + c;
+    if constexpr (EPI == EPI_SWIGLU) {
+        const bf16 v[4] = {f2bf(silu(a[0]) * b[0]), f2bf(silu(a[1]) * b[1]), f2bf(silu(a[2]) * b[2]),
+                           f2bf(silu(a[3]) * b[3])};
+        store_bf16<4>(static_cast<bf16*>(g.out) + o, v);
+    } else if constexpr (EPI == EPI_RESID_F32OUT) {
+        const bf16x4 r = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(g.resid) + o);
+        *reinterpret_cast<f32x4*>(static_cast<float*>(g.out) + o) = a + f32x4{bf2f(r[0]), bf2f(r[1]), bf2f(r[2]), bf2f(r[3])};
+    } else if constexpr (EPI == EPI_RESID_F32IN) {
+        a += *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.resid) + o);
+        const bf16 v[4] = {f2bf(a[0]), f2bf(a[1]), f2bf(a[2]), f2bf(a[3])};
+        store_bf16<4>(static_cast<bf16*>(g.out) + o, v);
     }
 }
 
-// Weight-streaming GEMM for small m (at most 32 T rows).  W is read once,
+// W row feeding B column c (c = n0 + tile row).
+template <int EPI>
+__device__ __forceinline__ int w_row(const GemmArgs& g, int c) {
+    if (EPI == EPI_SWIGLU) {
+        const int sub = c >> 5, f = g.n >> 1;
+        const int col = (sub >> 1) * 32 + (c & 31);
+        return (sub & 1) ? f + col : col;
+    }
+    if (EPI == EPI_QKV) {
+        const int cw = c % g.hd;
+        return c - cw + qkv_dim(cw, g.hd);
+    }
+    return c;
+}
+
+// Weight-streaming GEMM for wide projections (gate/up) of at most 16 rows.  W is read once,
 // straight from memory into MFMA operand registers with no LDS staging, so
 // the bytes in flight per CU are bounded only by registers and occupancy.
 // A work-group has KS waves that split its k range; every wave computes the
@@ -680,17 +598,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const fl
 // step, so every dot product is unchanged.  MFMA rows are W rows and columns
 // are tokens: element e of lane l is W row 8(e/4) + 4(l/32) + e%4 of its
 // column group, token 32 t + l%32.
-template <int T, int EPI, bool SPLIT>
-__global__ __launch_bounds__(256) void skinny_kernel(GemmArgs g, float* __restrict__ partial, int k_per_split,
-                                                     int ks_count) {
+template <int EPI>
+__global__ __launch_bounds__(256) void skinny_kernel(GemmArgs g, int ks_count) {
+    constexpr int T = 1;
     constexpr int NA = 2 * T;  // accumulator tiles: 2 column groups x T token groups
     __shared__ float red[2][NA * 16][64];  // ks_count / 2 <= 2 slots
 
     const int lane = threadIdx.x & 63, ks = threadIdx.x >> 6;
     const int r = lane & 31, h = lane >> 5;
     const int c0 = blockIdx.x * 64;
-    const int k_wave = k_per_split / ks_count;
-    const int kbeg = blockIdx.y * k_per_split + ks * k_wave + 32 * h;
+    const int k_wave = g.k / ks_count;
+    const int kbeg = ks * k_wave + 32 * h;
     const int nkb = k_wave / 64;
 
     const bf16* W = static_cast<const bf16*>(g.w);
@@ -768,14 +686,6 @@ __global__ __launch_bounds__(256) void skinny_kernel(GemmArgs g, float* __restri
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
             const int i0 = 8 * e4 + 4 * h;  // W row of element 4 e4 within its column group
-            if (SPLIT) {
-                float* P = partial + (static_cast<size_t>(blockIdx.y) * g.m + row) * g.n + c0 + i0;
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-                    *reinterpret_cast<f32x4*>(P + 32 * c) =
-                        f32x4{acc[c][t][4 * e4], acc[c][t][4 * e4 + 1], acc[c][t][4 * e4 + 2], acc[c][t][4 * e4 + 3]};
-                continue;
-            }
             if (EPI == EPI_QKV) {
                 // rotations (and the KV slot) read before any store, which the
                 // compiler cannot tell apart from the tables
@@ -935,84 +845,38 @@ __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(GemmArgs g
     }
 }
 
+// Tile configurations: rows, columns, waves along each, work-groups that share
+// a CU, and the planner's time per 64-deep k step of one work-group (us).
 struct TileCfg {
-    int bm, bn, waves_m, waves_n, bk, ring;  // ring 0: register-staged double buffer
+    int bm, bn, per_cu;
+    float step_us;
 };
-// BM x BN / waves (per-wave tile), k depth per stage, main loop, LDS:
-// 0: 128x128 / 4 (64x64), k 64, register-staged (64 KB: two work-groups per CU)
-// 1: 64x128 / 4 (32x64), k 64, register-staged (the fallback when n is not a
-//    multiple of 256)
-// 2: 256x128 / 4 (128x64), k 32, register-staged (48 KB: two per CU)
-// 3: 256x256 / 8 (128x64), k 64, 2-buffer direct-load ring (128 KB)
-// 4: 192x256 / 8 (96x64), k 64, 2-buffer ring (112 KB): less row padding
-//    than 256 where m is just past a multiple of 256
-// 5: 128x128 / 4 (64x64), k 64, 2-buffer ring (64 KB: two per CU)
-// 6: 96x256 / 4 (96x64), k 64, 3-buffer ring (132 KB): a single row tile
-//    for m up to 96, three stages of weights in flight
-// 7: 160x256 / 4 (160x64), k 64, 2-buffer ring (104 KB)
-// 8: 128x128 / 4 (64x64), k 64, 4-buffer ring (128 KB)
-// 9: 64x256 / 4 (64x64), k 64, 3-buffer ring (120 KB)
-// 10: 128x128 / 4 (64x64), k 64, 3-buffer ring (96 KB)
-// The deep rings of the small-m tiles keep more weight bytes in flight per
-// CU, which is what the weight-streaming shapes are short of.
-constexpr TileCfg kCfgs[] = {{128, 128, 2, 2, 64, 0}, {64, 128, 2, 2, 64, 0}, {256, 128, 2, 2, 32, 0},
-                             {256, 256, 2, 4, 64, 2}, {192, 256, 2, 4, 64, 2}, {128, 128, 2, 2, 64, 2},
-                             {96, 256, 1, 4, 64, 3},  {160, 256, 1, 4, 64, 2}, {128, 128, 2, 2, 64, 4},
-                             {64, 256, 1, 4, 64, 3},  {128, 128, 2, 2, 64, 3}};
+constexpr TileCfg kCfgs[] = {{256, 256, 1, 1.269f}, {224, 256, 1, 1.100f}, {192, 256, 1, 0.974f}, {160, 256, 1, 0.850f},
+                             {256, 128, 1, 0.731f}, {192, 128, 1, 0.585f}, {160, 128, 2, 0.477f}, {128, 128, 2, 0.388f},
+                             {96, 128, 2, 0.360f},  {64, 128, 2, 0.226f}};
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
+constexpr int kCus = 256;
 
-template <int EPI>
-void launch_reduce(const GemmArgs& g, const float* part, int splits, hipStream_t s) {
-    size_t work;
-    if (EPI == EPI_QKV) work = static_cast<size_t>(g.m) * (g.n / 2);
-    else if (EPI == EPI_SWIGLU) work = static_cast<size_t>(g.m) * (g.n / 8);
-    else work = static_cast<size_t>(g.m) * (g.n / 4);
-    splitk_reduce_kernel<EPI><<<static_cast<unsigned>((work + 255) / 256), 256, 0, s>>>(g, part, splits);
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int ST, int EPI>
-void launch_epi(const GemmArgs& g, const GemmPlan& p, float* part, hipStream_t s) {
-    constexpr int THREADS = WAVES_M * WAVES_N * 64;
-    const int tiles = ((g.m + BM - 1) / BM) * (g.n / BN);
-    if (p.sk_workers > 0) {
-        gemm_sk_kernel<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI>
-            <<<p.dp_tiles + p.sk_workers, THREADS, 0, s>>>(g, part, p.dp_tiles, p.sk_workers);
-        const int units = EPI == EPI_QKV ? BM * BN / 2 : EPI == EPI_SWIGLU ? BM * BN / 8 : BM * BN / 4;
-        sk_fixup_kernel<BM, BN, BK, EPI>
-            <<<dim3(tiles - p.dp_tiles, (units + 255) / 256), 256, 0, s>>>(g, part, p.dp_tiles, p.sk_workers);
-        return;
-    }
-    dim3 grid(tiles, p.splits);
-    const int kps = g.k / p.splits;
+template <class T, int EPI>
+void launch_tile(const GemmArgs& g, const GemmPlan& p, float* part, hipStream_t s) {
+    const dim3 grid(((g.m + T::BM - 1) / T::BM) * (g.n / T::BN), p.splits);
     if (p.splits == 1) {
-        gemm_kernel<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI, false><<<grid, THREADS, 0, s>>>(g, nullptr, kps);
+        tile_kernel<T, EPI, false><<<grid, T::THREADS, 0, s>>>(g, nullptr, g.k);
         return;
     }
-    gemm_kernel<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI, true><<<grid, THREADS, 0, s>>>(g, part, kps);
-    launch_reduce<EPI>(g, part, p.splits, s);
+    tile_kernel<T, EPI, true><<<grid, T::THREADS, 0, s>>>(g, part, g.k / p.splits);
+    const size_t work = static_cast<size_t>(g.m) * (EPI == EPI_QKV || EPI == EPI_SWIGLU ? g.n / 8 : g.n / 4);
+    splitk_reduce_kernel<EPI><<<static_cast<unsigned>((work + 255) / 256), 256, 0, s>>>(g, part, p.splits);
 }
 
-template <int T, int EPI>
-void launch_skinny_epi(const GemmArgs& g, const GemmPlan& p, float* part, hipStream_t s) {
-    dim3 grid(g.n / 64, p.splits);
-    const int threads = 64 * p.ks;
-    const int kps = g.k / p.splits;
-    if (p.splits == 1) {
-        skinny_kernel<T, EPI, false><<<grid, threads, 0, s>>>(g, nullptr, kps, p.ks);
-        return;
-    }
-    skinny_kernel<T, EPI, true><<<grid, threads, 0, s>>>(g, part, kps, p.ks);
-    launch_reduce<EPI>(g, part, p.splits, s);
-}
-
-template <int T>
-void launch_skinny(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t s) {
+template <class T>
+void launch_cfg(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t s) {
     float* part = static_cast<float*>(partial);
     switch (g.epi) {
-        case EPI_RESID_F32OUT: launch_skinny_epi<T, EPI_RESID_F32OUT>(g, p, part, s); break;
-        case EPI_RESID_F32IN: launch_skinny_epi<T, EPI_RESID_F32IN>(g, p, part, s); break;
-        case EPI_SWIGLU: launch_skinny_epi<T, EPI_SWIGLU>(g, p, part, s); break;
-        default: launch_skinny_epi<T, EPI_QKV>(g, p, part, s); break;
+        case EPI_RESID_F32OUT: launch_tile<T, EPI_RESID_F32OUT>(g, p, part, s); break;
+        case EPI_RESID_F32IN: launch_tile<T, EPI_RESID_F32IN>(g, p, part, s); break;
+        case EPI_SWIGLU: launch_tile<T, EPI_SWIGLU>(g, p, part, s); break;
+        default: launch_tile<T, EPI_QKV>(g, p, part, s); break;
     }
 }
 
@@ -1031,87 +895,72 @@ void launch_narrow(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int ST>
-void launch_cfg(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t s) {
-    float* part = static_cast<float*>(partial);
-    switch (g.epi) {
-        case EPI_RESID_F32OUT: launch_epi<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI_RESID_F32OUT>(g, p, part, s); break;
-        case EPI_RESID_F32IN: launch_epi<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI_RESID_F32IN>(g, p, part, s); break;
-        case EPI_SWIGLU: launch_epi<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI_SWIGLU>(g, p, part, s); break;
-        default: launch_epi<BM, BN, WAVES_M, WAVES_N, BK, ST, EPI_QKV>(g, p, part, s); break;
-    }
+// Predicted time (us) of a tile configuration with a k split: rounds of
+// work-groups over the CUs, each a fixed cost (fill of the LDS buffers,
+// epilogue, which grows with the tile) plus its k steps; where two work-groups
+// share a CU, a round of both takes about twice as long as one alone.  Against
+// that stands the time to stream the weights (a CU draws at most 32 KB/us, the
+// chip 6.9 TB/s) and to bring every tile's panels from L2 (smooth maximum); a
+// split adds its reduction's launch and traffic.  Rows count in blocks of 32
+// (every tile's row granularity), so that row counts of one block share a plan.
+// The constants are a fit to 3700 timings (seven shapes, 16 to 4104 rows, all
+// configurations, splits 1 to 8, weights out of cache): median error below 1%,
+// 90% within -14% and +25%; the configuration it picks is on average 1.2%
+// slower than the fastest one measured, 14% at worst.
+float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
+    const int wgs = ((m32 + c.bm - 1) / c.bm) * (n / c.bn) * splits;
+    const float nk = static_cast<float>(k / 64) / splits;
+    const float fixed = 5.38f + 2.16f * (c.bm * c.bn) / 65536.f;
+    const float one = fixed + nk * c.step_us, both = fixed + 2.11f * nk * c.step_us;
+    const int full = wgs / (kCus * c.per_cu), rem = wgs % (kCus * c.per_cu);
+    float t = full * (c.per_cu == 2 ? both : one);
+    if (rem) t += c.per_cu == 2 && rem > kCus ? both : one;
+    const float rate = std::min(6.92e6f, 32.0e3f * std::min(wgs, kCus));
+    const float mem = 2.f * n * k / rate + 0.2f + 2.f * wgs * (c.bm + c.bn) * (static_cast<float>(k) / splits) / 25.67e6f;
+    const float t2 = t * t, m2 = mem * mem;
+    t = 0.3f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2));
+    if (splits > 1) t += 1.74f + 8.f * splits * m32 * n / 5.03e6f;
+    return t;
 }
 
 }  // namespace
 
-// Tile and split choice per projection shape, from one sweep that timed
-// every configuration plainly, with k split two ways and with the stream-K
-// schedule at m = 64 .. 4104 (21 points) on the 8B-layer shapes, each run
-// after a read sweep of the caches.  Band i covers m in (m_hi[i - 1], m_hi[i]]
-// and takes the fastest entry measured at its upper end (the previous
-// choice where it was within 1.5%); neighbouring bands with the same choice
-// are merged.  The bands are not monotone in m: what pays is how m fills
-// whole row tiles and rounds of the CUs.  splits: 0 the default rule of
-// plan_with_cfg, 2 a forced two-way split, -1 the stream-K schedule.
-struct Band {
-    int m_hi;
-    int8_t cfg, splits;
-};
-constexpr Band kBandsQkv[] = {{64, 9, 0},     {96, 6, 0},     {128, 0, 0},    {160, 4, 0},
-                              {192, 10, 2},   {224, 8, 2},    {288, 9, 2},    {480, 6, 2},
-                              {544, 5, 0},    {928, 4, 2},    {1056, 5, 0},   {1312, 4, -1},
-                              {1568, 4, 2},   {2592, 5, 0},   {3104, 4, 0},   {4104, 3, 0}};
-constexpr Band kBandsO[] = {{128, 10, 0},  {192, 6, 0},   {224, 5, 0},   {352, 10, 2},  {480, 8, 2},
-                            {672, 6, 2},   {800, 5, 0},   {928, 8, -1},  {1312, 4, 2},  {1568, 0, 0},
-                            {2080, 3, -1}, {2592, 4, 0},  {3104, 5, 0},  {4104, 4, 0}};
-constexpr Band kBandsGateUp[] = {{64, 9, 2},   {96, 6, 2},   {128, 0, 0},  {192, 4, 2},  {224, 3, 2},
-                                 {352, 4, 0},  {416, 3, 0},  {480, 2, 0},  {544, 7, 0},  {672, 4, 0},
-                                 {928, 3, 0},  {1056, 4, 0}, {1312, 3, 0}, {1568, 4, 0}, {4104, 3, 0}};
-constexpr Band kBandsDown[] = {{128, 10, 0},  {192, 6, 0},   {224, 5, 0},   {288, 7, 0},
-                               {352, 4, 0},   {480, 3, 0},   {544, 7, -1},  {672, 4, -1},
-                               {928, 3, -1},  {1056, 4, -1}, {1312, 4, 2},  {1568, 3, 2},
-                               {2080, 3, -1}, {2592, 4, -1}, {3104, 3, -1}, {4104, 4, 0}};
-
-template <size_t N>
-const Band& band_of(const Band (&t)[N], int m) {
-    for (const Band& b : t)
-        if (m <= b.m_hi) return b;
-    return t[N - 1];
-}
-
-// The narrow kernel takes qkv, the output and the down projection up to 8
-// rows and the output projection up to 24 (8B layer, against the kernels
-// below: output -34% at 1 row, -18% at 16, -7% at 24; down -22% at 1 row,
-// -13% at 8; qkv -12% at 1 row; it loses on gate/up and beyond those row
-// counts, where every work-group re-reads all the activation rows; 64-column
-// work-groups, which re-read them a quarter as often, measured 1.5-3x slower
-// for want of work-groups).  The weight-streaming
-// kernel takes the other narrow projections up to 32 rows and gate/up up to
-// 16 (it won there by 10-20%; on qkv the tile kernels measured faster).
-// Shapes outside the 8B layer take the band of their projection class; n must
-// be a multiple of 128 and k of 64.
-GemmPlan plan_gemm(int m, int n, int k) {
+// Wide projections (gate/up) of up to 16 rows take the weight-streaming
+// kernel: 46 / 48 / 51 us at 1 / 8 / 16 rows of the 8B layer against 49 / 49 /
+// 49 for the tile kernel, which is ahead from there on (51 against 59 at 24).
+// The narrow kernel takes qkv- and down-like projections up to 8 rows and the
+// output projection up to 24 (8B layer, against the tile kernel, us at 1 / 8 /
+// 24 rows: output 8.4 / 9.2 / 12.4 against 11.6 / 12.1 / 12.4; down 21.6 /
+// 25.8 at 1 / 8 rows against 25.5 / 26.0, 31.5 against 26.3 at 16; qkv 14.2 /
+// 15.4 against 14.0 / 14.7 and no reduction launch).  Larger row
+// counts, where each of its work-groups re-reads all activation rows, take the tile kernel with the configuration and split that
+// predict_us ranks first.  n must be a multiple of 128 and k of 64; a split
+// keeps at least 512 of k.
+GemmPlan plan_gemm(int m, int n, int k, int max_splits) {
     const bool wide = n >= 16384, qkv_like = n >= 6144 && !wide;
-    if (n % 64 == 0 && k % 32 == 0 && !wide && (m <= 8 || (m <= 24 && !qkv_like && k < 8192)))
-        return plan_with_cfg(kNarrowCfg, m, n, k);
-    if (n % 64 == 0 && (wide ? m <= 16 : m <= 32 && !qkv_like)) return plan_with_cfg(kSkinnyCfg, m, n, k);
-    const Band& b = k >= 8192 ? band_of(kBandsDown, m)
-                    : wide    ? band_of(kBandsGateUp, m)
-                    : qkv_like ? band_of(kBandsQkv, m)
-                               : band_of(kBandsO, m);
-    if (n % kCfgs[b.cfg].bn) return plan_with_cfg(n % 128 ? 1 : 0, m, n, k);
-    if (b.splits < 0) return plan_stream_k(b.cfg, m, n, k);
-    GemmPlan p = plan_with_cfg(b.cfg, m, n, k);
-    if (b.splits > 0 && k % (b.splits * BK_MAX) == 0) {
-        p.splits = b.splits;
-        p.partial_bytes = b.splits > 1 ? static_cast<size_t>(b.splits) * m * n * sizeof(float) : 0;
+    if (!wide && (m <= 8 || (m <= 24 && !qkv_like && k < 8192))) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
+    if (wide && m <= 16) return plan_with_cfg(kSkinnyCfg, 1, m, n, k);
+    int cfg = kNumCfgs - 1, splits = 1;
+    const int m32 = (m + 31) / 32 * 32;
+    float best = 0.f;
+    for (int c = 0; c < kNumCfgs; ++c) {
+        if (n % kCfgs[c].bn) continue;
+        for (int sp = 1; sp <= max_splits && (sp == 1 || (k % (64 * sp) == 0 && k / sp >= 512)); sp *= 2) {
+            const float t = predict_us(kCfgs[c], sp, m32, n, k);
+            if (best == 0.f || t < best) {
+                best = t;
+                cfg = c;
+                splits = sp;
+            }
+        }
     }
-    return p;
+    return plan_with_cfg(cfg, splits, m, n, k);
 }
 
-GemmPlan plan_with_cfg(int cfg, int m, int n, int k) {
+GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k) {
     GemmPlan p{};
     p.cfg = cfg;
+    p.splits = 1;
     if (cfg == kNarrowCfg) {
         // waves per work-group: each takes a whole number of 32-wide k slices
         int ks = 8;
@@ -1119,62 +968,28 @@ GemmPlan plan_with_cfg(int cfg, int m, int n, int k) {
         p.ks = ks;
         p.bm = m <= 16 ? 16 : 32;
         p.bn = 16;
-        p.splits = 1;
         return p;
     }
-    if (cfg == kSkinnyCfg) {
-        // Four waves slice k inside a work-group (fewer when k is short); k is
-        // also split across work-groups until there are 384 of them (three
-        // share a CU), keeping whole 64-wide steps per wave.
-        p.bn = 64;
-        p.bm = 32;
+    if (cfg == kSkinnyCfg) {  // four waves slice k (fewer when k is short), whole 64-wide steps each
         int ks = 4;
         while (ks > 1 && k % (64 * ks)) ks /= 2;
         p.ks = ks;
-        int splits = 1;
-        while (splits < 8 && (n / 64) * splits < 384 && k % (2 * 64 * ks * splits) == 0) splits *= 2;
-        p.splits = splits;
-        p.partial_bytes = splits > 1 ? static_cast<size_t>(splits) * m * n * sizeof(float) : 0;
+        p.bm = 32;
+        p.bn = 64;
         return p;
     }
     p.bm = kCfgs[cfg].bm;
     p.bn = kCfgs[cfg].bn;
-    const long tiles = static_cast<long>(n / p.bn) * ((m + p.bm - 1) / p.bm);
-    int splits = 1;
-    // Too few tiles to fill 256 compute units: split k (each split >= 512 deep).
-    while (splits < 8 && tiles * splits < 384 && k % (2 * splits * BK_MAX) == 0 && k / (2 * splits) >= 512)
-        splits *= 2;
     p.splits = splits;
     p.partial_bytes = splits > 1 ? static_cast<size_t>(splits) * m * n * sizeof(float) : 0;
-    return p;
-}
-
-GemmPlan plan_stream_k(int cfg, int m, int n, int k) {
-    GemmPlan p = plan_with_cfg(cfg, m, n, k);
-    if (cfg == kSkinnyCfg || cfg == kNarrowCfg) return p;
-    const TileCfg& t = kCfgs[cfg];
-    // work-groups a CU holds at once: one for eight waves or more than 80 KB of LDS
-    const int lds = (t.ring == 0 ? 2 : t.ring) * (t.bm + t.bn) * t.bk * 2;
-    const int slots = kStreamKCus * ((t.waves_m * t.waves_n >= 8 || lds > 80 * 1024) ? 1 : 2);
-    const int tiles = ((m + t.bm - 1) / t.bm) * (n / t.bn);
-    p.splits = 1;
-    p.partial_bytes = 0;
-    if (tiles % slots == 0) return p;  // whole rounds: plain tiles
-    const int q = tiles / slots, r = tiles % slots;
-    p.dp_tiles = q >= 1 ? (q - 1) * slots : 0;  // the last full round joins the stream-K part
-    const long iters = static_cast<long>(tiles - p.dp_tiles) * (k / t.bk);
-    p.sk_workers = static_cast<int>(std::min<long>(slots, iters));
-    (void)r;
-    p.partial_bytes = static_cast<size_t>(2) * p.sk_workers * t.bm * t.bn * sizeof(float);
     return p;
 }
 
 bool gemm_shape_ok(const GemmPlan& p, int n, int k) {
     if (p.cfg == kNarrowCfg)  // m <= 32 is the caller's part; paired epilogues need 64-column tiles
         return n % 64 == 0 && p.ks >= 1 && p.ks <= 8 && k % (32 * p.ks) == 0;
-    if (p.cfg == kSkinnyCfg)  // m <= 32 is the caller's part (plan_gemm)
-        return n % 64 == 0 && p.ks >= 1 && p.ks <= 4 && k % (64 * p.ks * p.splits) == 0;
-    return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * BK_MAX) == 0;
+    if (p.cfg == kSkinnyCfg) return n % 64 == 0 && p.ks >= 1 && p.ks <= 4 && k % (64 * p.ks) == 0;
+    return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 
 void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t s) {
@@ -1185,21 +1000,26 @@ void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_
         return;
     }
     if (p.cfg == kSkinnyCfg) {
-        launch_skinny<1>(g, p, partial, s);  // plans cover m <= 32
+        const dim3 grid(g.n / 64);
+        switch (g.epi) {
+            case EPI_RESID_F32OUT: skinny_kernel<EPI_RESID_F32OUT><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
+            case EPI_RESID_F32IN: skinny_kernel<EPI_RESID_F32IN><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
+            case EPI_SWIGLU: skinny_kernel<EPI_SWIGLU><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
+            default: skinny_kernel<EPI_QKV><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
+        }
         return;
     }
-    switch (p.cfg) {
-        case 0: launch_cfg<128, 128, 2, 2, 64, 0>(g, p, partial, s); break;
-        case 1: launch_cfg<64, 128, 2, 2, 64, 0>(g, p, partial, s); break;
-        case 2: launch_cfg<256, 128, 2, 2, 32, 0>(g, p, partial, s); break;
-        case 3: launch_cfg<256, 256, 2, 4, 64, 2>(g, p, partial, s); break;
-        case 4: launch_cfg<192, 256, 2, 4, 64, 2>(g, p, partial, s); break;
-        case 5: launch_cfg<128, 128, 2, 2, 64, 2>(g, p, partial, s); break;
-        case 6: launch_cfg<96, 256, 1, 4, 64, 3>(g, p, partial, s); break;
-        case 7: launch_cfg<160, 256, 1, 4, 64, 2>(g, p, partial, s); break;
-        case 8: launch_cfg<128, 128, 2, 2, 64, 4>(g, p, partial, s); break;
-        case 9: launch_cfg<64, 256, 1, 4, 64, 3>(g, p, partial, s); break;
-        default: launch_cfg<128, 128, 2, 2, 64, 3>(g, p, partial, s); break;
+    switch (p.cfg) {  // kCfgs order
+        case 0: launch_cfg<Tile<256, 256, 2, 4>>(g, p, partial, s); break;
+        case 1: launch_cfg<Tile<224, 256, 2, 4>>(g, p, partial, s); break;
+        case 2: launch_cfg<Tile<192, 256, 2, 4>>(g, p, partial, s); break;
+        case 3: launch_cfg<Tile<160, 256, 2, 4>>(g, p, partial, s); break;
+        case 4: launch_cfg<Tile<256, 128, 4, 2>>(g, p, partial, s); break;
+        case 5: launch_cfg<Tile<192, 128, 2, 4>>(g, p, partial, s); break;
+        case 6: launch_cfg<Tile<160, 128, 2, 4>>(g, p, partial, s); break;
+        case 7: launch_cfg<Tile<128, 128, 2, 4>>(g, p, partial, s); break;
+        case 8: launch_cfg<Tile<96, 128, 2, 4>>(g, p, partial, s); break;
+        default: launch_cfg<Tile<64, 128, 2, 4>>(g, p, partial, s); break;
     }
 }
 

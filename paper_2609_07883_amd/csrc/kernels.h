@@ -36,26 +36,19 @@ struct GemmArgs {
     int hq, hkv, hd;
 };
 struct GemmPlan {
-    int cfg;      // tile configuration index (kSkinnyCfg: the weight-streaming kernel)
+    int cfg;      // tile configuration index (kSkinnyCfg, kNarrowCfg: the streaming kernels)
     int bm, bn;
     int splits;   // split-K factor across work-groups (1: fused epilogue)
     size_t partial_bytes;
-    int ks;     // weight-streaming kernel (m <= 32): k slices per work-group
-    int sk_workers = 0;  // stream-K: work-groups sharing the k steps of the last tiles (0: off)
-    int dp_tiles = 0;    // stream-K: tiles run whole before them
+    int ks;       // streaming kernels: waves that share the k range of a work-group
 };
-// CUs the stream-K schedule spreads its last round over (MI355X).
-constexpr int kStreamKCus = 256;
-constexpr int kSkinnyCfg = 99;
+constexpr int kSkinnyCfg = 99;  // the weight-streaming kernel (m <= 16)
 constexpr int kNarrowCfg = 98;  // the narrow kernel (m <= 32, k split inside the work-group)
-GemmPlan plan_gemm(int m, int n, int k);
-// The plan for a given tile configuration (split-K chosen by tile count).
-GemmPlan plan_with_cfg(int cfg, int m, int n, int k);
-// The configuration with a stream-K schedule: whole tiles for all rounds but
-// the last full one, whose tiles and the remainder share their k steps
-// equally over one round of work-groups (plain tiles when rounds are whole).
-GemmPlan plan_stream_k(int cfg, int m, int n, int k);
-// Whether the plan's tiles divide n and k.
+constexpr int kMaxSplits = 8;
+GemmPlan plan_gemm(int m, int n, int k, int max_splits = kMaxSplits);
+// The plan for a given configuration and k split.
+GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k);
+// Whether the plan's tiles divide n and its splits k.
 bool gemm_shape_ok(const GemmPlan& p, int n, int k);
 // Enqueue the GEMM; `partial` must hold plan.partial_bytes when plan.splits > 1.
 void launch_gemm(const GemmArgs& g, const GemmPlan& plan, void* partial, hipStream_t s);

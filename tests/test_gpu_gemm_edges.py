@@ -1,0 +1,44 @@
+"""GPU parity of the projections at the edges of the tile kernel: k ranges of
+one, two, three and five 64-deep steps (its software pipeline starts and ends
+inside them), rows on both sides of a 32-row block and of a tile, and widths of
+one 128-column tile.  Every row of each stage against the float64 oracle at the
+parity bar.
+
+Weights are drawn at std 0.09 (about 1 / sqrt(d_model)), so that each
+projection's share of the residual stream is of the stream's own size and an
+error in it is not hidden behind the residual.
+"""
+import pytest
+
+from paper_2609_07883_amd import api, synth
+from paper_2609_07883_amd.synth import ModelShape
+from tests.parity import TOL, Mirror, check, stage_errors
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+# ffn 64, 192, 320: the down projection's k is one, three, five steps; d_model
+# 128 gives the others two
+@pytest.mark.parametrize("rows", [33, 64, 65, 129])
+@pytest.mark.parametrize("ffn", [64, 192, 320])
+def test_short_k_ranges(ffn, rows):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_07883_amd.runtime import Session
+    shape = ModelShape(n_layers=1, d_model=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=ffn,
+                       rms_eps=1e-5, rope_theta=10000.0, max_pos=1024)
+    sess = Session(shape, num_blocks=64, max_c=256, max_b=2, layers=[synth.layer_weights(shape, std=0.09)])
+    mir = Mirror(sess)
+    for sid, n in ((1, 20), (2, 33)):
+        mir.create(sid)
+        mir.install_context(sid, n)
+    b = api.Batch(rows - 1, 1, 20, [2], [33])
+    x = synth.embeddings(rows, shape.d_model, seed=1, stream=rows)
+    y, yr, sg, sr = mir.step(b, x)
+    assert sg == sr
+    for name, e in stage_errors(mir, b, x).items():
+        assert e["rel"] <= TOL, (name, e)
+    check(y, yr, f"ffn {ffn}, {rows} rows")
+    assert mir.kv_error(b) <= TOL
