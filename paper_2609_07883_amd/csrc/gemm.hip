@@ -851,9 +851,9 @@ struct TileCfg {
     int bm, bn, per_cu;
     float step_us;
 };
-constexpr TileCfg kCfgs[] = {{256, 256, 1, 1.269f}, {224, 256, 1, 1.100f}, {192, 256, 1, 0.974f}, {160, 256, 1, 0.850f},
-                             {256, 128, 1, 0.731f}, {192, 128, 1, 0.585f}, {160, 128, 2, 0.477f}, {128, 128, 2, 0.388f},
-                             {96, 128, 2, 0.360f},  {64, 128, 2, 0.226f}};
+constexpr TileCfg kCfgs[] = {{256, 256, 1, 1.253f}, {224, 256, 1, 1.108f}, {192, 256, 1, 0.990f}, {160, 256, 1, 0.874f},
+                             {256, 128, 1, 0.715f}, {192, 128, 1, 0.628f}, {160, 128, 2, 0.519f}, {128, 128, 2, 0.460f},
+                             {96, 128, 2, 0.435f},  {64, 128, 2, 0.396f}};
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr int kCus = 256;
 
@@ -900,26 +900,29 @@ void launch_narrow(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
 // epilogue, which grows with the tile) plus its k steps; where two work-groups
 // share a CU, a round of both takes about twice as long as one alone.  Against
 // that stands the time to stream the weights (a CU draws at most 32 KB/us, the
-// chip 6.9 TB/s) and to bring every tile's panels from L2 (smooth maximum); a
+// chip 6.7 TB/s) and to bring every tile's panels from L2 (smooth maximum); a
 // split adds its reduction's launch and traffic.  Rows count in blocks of 32
 // (every tile's row granularity), so that row counts of one block share a plan.
-// The constants are a fit to 3700 timings (seven shapes, 16 to 4104 rows, all
-// configurations, splits 1 to 8, weights out of cache): median error below 1%,
-// 90% within -14% and +25%; the configuration it picks is on average 1.2%
-// slower than the fastest one measured, 14% at worst.
+// The constants are a fit to 3500 timings (eleven shapes, 16 to 4104 rows, all
+// configurations, splits 1 to 8; activations in cache, weights cycled through
+// 700 MB so that none are: a layer finds them so, and fitted to weights in the
+// last-level cache the rule picked tiles 20-40% slower for the output and qkv
+// projections at 288 rows): median error below 1%, 90% within -11% and +13%;
+// the configuration it picks is on average 0.7% slower than the fastest one
+// measured, 18% at worst.
 float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
     const int wgs = ((m32 + c.bm - 1) / c.bm) * (n / c.bn) * splits;
     const float nk = static_cast<float>(k / 64) / splits;
-    const float fixed = 5.38f + 2.16f * (c.bm * c.bn) / 65536.f;
-    const float one = fixed + nk * c.step_us, both = fixed + 2.11f * nk * c.step_us;
+    const float fixed = 4.18f + 2.66f * (c.bm * c.bn) / 65536.f;
+    const float one = fixed + nk * c.step_us, both = fixed + 1.91f * nk * c.step_us;
     const int full = wgs / (kCus * c.per_cu), rem = wgs % (kCus * c.per_cu);
     float t = full * (c.per_cu == 2 ? both : one);
     if (rem) t += c.per_cu == 2 && rem > kCus ? both : one;
-    const float rate = std::min(6.92e6f, 32.0e3f * std::min(wgs, kCus));
-    const float mem = 2.f * n * k / rate + 0.2f + 2.f * wgs * (c.bm + c.bn) * (static_cast<float>(k) / splits) / 25.67e6f;
+    const float rate = std::min(6.73e6f, 32.0e3f * std::min(wgs, kCus));
+    const float mem = 2.f * n * k / rate + 0.2f + 2.f * wgs * (c.bm + c.bn) * (static_cast<float>(k) / splits) / 40.59e6f;
     const float t2 = t * t, m2 = mem * mem;
-    t = 0.3f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2));
-    if (splits > 1) t += 1.74f + 8.f * splits * m32 * n / 5.03e6f;
+    t = 0.91f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2));
+    if (splits > 1) t += 2.18f + 8.f * splits * m32 * n / 4.68e6f;
     return t;
 }
 
