@@ -12,8 +12,7 @@
  *     pointers are ordinary CPU memory.  The library never allocates device
  *     memory: weights, KV pools, activations and the workspace all belong to
  *     the caller.  It owns only host state (sequence tables, cost tables) plus
- *     a small pinned host staging ring, HIP events and one non-blocking
- *     stream (decode attention beside a long chunk's), created on first use,
+ *     a small pinned host staging ring and HIP events, created on first use,
  *     and the static workspace array of slw_mixed_iteration_static, which is
  *     part of its device code (loaded with it, never allocated by a call).
  *   - Streams are passed as void* holding a hipStream_t (NULL = the null
@@ -191,9 +190,7 @@ int slw_workspace_size(slw_ctx* ctx, int32_t max_C, int32_t max_B, size_t* bytes
  * a coherent pinned staging ring that a first kernel copies into the
  * workspace, then enqueues per layer: RMSNorm, QKV GEMM
  * whose epilogue applies RoPE and appends K/V to the pages, chunk attention
- * and split decode attention (one launch; for a chunk of at least 8 M
- * query-key pairs, decode attention on the context's own stream beside it,
- * joined back to `stream` by an event before the merge), output GEMM +
+ * and split decode attention (one launch) and their merge, output GEMM +
  * residual (kept in fp32 within the layer), RMSNorm, gate/up GEMM with
  * SiLU*mul, down GEMM + residual.
  * Each row's K/V is written at slot(seq, pos) = bt[pos/16]*16 + pos%16 of its
@@ -209,7 +206,7 @@ int slw_mixed_iteration(slw_ctx* ctx, const slw_batch* batch, const void* x_in, 
  * slw_mixed_iteration, but it takes no workspace: it uses a device array of
  * SLW_STATIC_WS_BYTES inside the library, one per GPU, which each GPU the
  * library runs on holds until the process ends.  The call allocates nothing
- * (no hipMalloc, no pinned host memory, no stream or event): the metadata is
+ * (no hipMalloc, no pinned host memory, no event): the metadata is
  * copied from host memory the context already holds, `stream` is
  * synchronised once after that copy (the iteration's kernels then run
  * asynchronously), both attentions run on `stream`, and no stage timing is

@@ -16,6 +16,8 @@
 //   V: [hd][16]         element (t, d) at d*16 + t
 #include <math.h>
 
+#include <type_traits>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -512,6 +514,364 @@ __global__ __launch_bounds__(512) void chunk_attn_kernel(ChunkAttnArgs a, Decode
     }  // items of this work-group
 }
 
+// ---------------------------------------------------------------------------
+// Chunk attention for long chunks, two wave groups half a tile apart.
+//
+// The same work, layouts and arithmetic as chunk_attn_kernel.  There, the two
+// waves of a SIMD meet at a barrier once a tile and run the same stage side by
+// side, so the matrix cores idle while both do softmax (MFMA busy 54%).  Here a
+// tile's work is two phases with a barrier after each:
+//   P1(t)  mask, running max, exponentials, P in bf16        (VALU)
+//   P2(t)  P V of tile t, then the scores of tile t + 1      (matrix cores)
+// and waves 4-7 run one phase behind waves 0-3 (one extra barrier at an item's
+// start, and waves 0-3 one at its end), so that on every SIMD one wave's
+// softmax runs under the other's products, with one copy of the code and no
+// register held across phases that the plain order would not hold.  Every wave
+// computes every tile of its item, masked where the tile lies past its rows:
+// branches around the phases cost 83 spilled registers.
+//
+// One wave per SIMD must keep the matrix cores fed in P2, so its LDS reads run
+// two fragment groups ahead, the first two already in P1, and its direct loads
+// are spread between the groups (issued together they hold up the MFMAs behind
+// them: 1790 -> 1624 us with the next point).  K and V have rings of four
+// 16 KB tiles (128 KB).  In slots (phases of waves 0-3), P2(t) of the two
+// groups, slots 2t + 2 and 2t + 3, reads V(t) and K(t + 1) and loads V(t + 3)
+// and K(t + 4) into the buffers of V(t - 1) and K(t), last read in slot 2t + 1;
+// V(t + 1) and K(t + 2) are published by the barrier that ends slot 2t + 2, one
+// slot before their first reader, every wave having waited for its own.
+//
+// 4096 rows at a 28 K prefix, 8B layer, alone: 1670 -> 1589 us (1.23 -> 1.30
+// PFLOP/s; 1.42 with the softmax left out, about what the power limit leaves
+// the projections too); 2048 rows at 8 K: 278 -> 264 us.  Short chunks lose by
+// the extra slots per item (700 rows at 1000: 30 -> 34 us) and stay with
+// chunk_attn_kernel.
+// ---------------------------------------------------------------------------
+template <int HD, int GROUP, bool DECODE>
+__global__ __launch_bounds__(512) void chunk_attn_pp_kernel(ChunkAttnArgs a, DecodeAttnArgs da) {
+    if constexpr (DECODE) {  // as in chunk_attn_kernel
+        const int n_chunk = a.n_slots * a.hkv;
+        if (static_cast<int>(blockIdx.x) >= n_chunk) {
+            const int v = (static_cast<int>(blockIdx.x) - n_chunk) * 8 +
+                          __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+            if (v < da.n_slots * da.hkv) decode_attn_wave<HD>(da, v % da.n_slots, v / da.n_slots, threadIdx.x & 63);
+            return;
+        }
+    }
+    constexpr int KK = HD / 32, NT = HD / 16, PAGE = HD * 16;
+    constexpr int LW = 4 * PAGE / 512 / 8;  // 1 KB loads of each of K and V that a wave issues per tile
+    static_assert(4 * PAGE % 4096 == 0 && NT % 4 == 0, "loads split evenly; V fragments are read four at a time");
+    constexpr int CT = 2;               // 16-row column tiles per wave (32 rows)
+    constexpr int PW = 32 / GROUP;      // positions per wave
+    constexpr float kSlack = 8.0f;      // lazy rescaling threshold, as in chunk_attn_kernel
+    __shared__ __attribute__((aligned(16))) bf16 Ks[4][4 * PAGE];
+    __shared__ __attribute__((aligned(16))) bf16 Vs[4][4 * PAGE];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int behind = wave >> 2;  // 1: the group that runs one phase behind
+    const int grp = lane >> 4, col = lane & 15;
+    const int pos = xcd_order(blockIdx.x, a.n_slots * a.hkv);
+    const int kvh = pos / a.n_slots, slot = pos % a.n_slots;
+    const float sl2 = kLog2e / sqrtf(static_cast<float>(HD));
+    const bf16* kpool = static_cast<const bf16*>(a.k_pool);
+    const bf16* vpool = static_cast<const bf16*>(a.v_pool);
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = bf16(1.0f);
+
+    // Load i of a wave covers slab j = wave + 8 i of K and of V: page j / KK,
+    // dims 32 (j % KK) .. + 31 of 16 tokens.
+    int l_page[LW], l_k[LW], l_v[LW], l_dst[LW];
+#pragma unroll
+    for (int i = 0; i < LW; ++i) {
+        const int j = wave + 8 * i, p = j / KK, slab = j % KK;
+        l_page[i] = p;
+        const int t = lane >> 2, sub = kswz(t, lane & 3);
+        l_k[i] = slab * 512 + t * 32 + sub * 8;
+        const int d = slab * 32 + (lane >> 1), h = (lane & 1) ^ ((d >> 2) & 1);
+        l_v[i] = d * 16 + h * 8;
+        l_dst[i] = p * PAGE + slab * 512;
+    }
+    const int i0 = a.slot_off[slot], i1 = a.slot_off[slot + 1];
+    for (int k = i0; k < i1; ++k) {
+        const int item = a.slot_items[k];
+        const int qt = a.item_qt[item], kb = a.item_kb[item], ke = a.item_ke[item];
+        const int row0 = a.qt_row0[qt], nrows = a.qt_rows[qt], pos0 = a.qt_pos0[qt];
+        const const_i32* bt_s = (const const_i32*)(a.bt + a.qt_bt[qt]);
+        const int j0 = wave * PW;
+        const int n_tiles = (ke - kb + 63) / 64;
+        const int wave_qpos_lo = pos0 + j0;
+        const bool wave_live = j0 < nrows;
+        const bool whole = a.qt_off[qt + 1] - a.qt_off[qt] == 1;
+
+        bf16x8 qf[CT][KK];
+        const bf16* qkv = static_cast<const bf16*>(a.qkv);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            const int r = ct * 16 + col, j = j0 + r / GROUP, h = kvh * GROUP + r % GROUP;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+                qf[ct][kk] = j < nrows ? *reinterpret_cast<const bf16x8*>(
+                                             qkv + static_cast<size_t>(row0 + j) * a.ld_qkv + h * HD + kk * 32 + grp * 8)
+                                       : bf16x8{};
+        }
+
+        // Block ids of the pages a wave's loads read, through the scalar cache:
+        // blk_k of the tile whose K is loaded next, blk_v of the one before it,
+        // whose V is loaded at the same time.
+        const int last_page = (ke - 1) >> 4;
+        int blk_k[LW], blk_v[LW];
+        auto fetch = [&](int t) {
+#pragma unroll
+            for (int i = 0; i < LW; ++i)
+                blk_k[i] = bt_s[__builtin_amdgcn_readfirstlane(min((kb >> 4) + 4 * t + l_page[i], last_page))];
+        };
+        auto load_k = [&](int i, int t) {
+            load_lds16(kpool + (static_cast<size_t>(blk_k[i]) * a.hkv + kvh) * PAGE + l_k[i], &Ks[t & 3][l_dst[i]]);
+        };
+        auto load_v = [&](int i, int t) {
+            load_lds16(vpool + (static_cast<size_t>(blk_v[i]) * a.hkv + kvh) * PAGE + l_v[i], &Vs[t & 3][l_dst[i]]);
+        };
+        auto next_ids = [&](int t) {  // the ids move up by a tile; tile t's come in
+#pragma unroll
+            for (int i = 0; i < LW; ++i) blk_v[i] = blk_k[i];
+            fetch(t);
+        };
+        // On the item's last V tile, the values of keys at or past ke
+        // (unwritten slots, stand-in pages) are zeroed in the 16-byte pieces
+        // the lane itself loaded, so that whatever the pool holds there cannot
+        // turn a zero probability into NaN in the P V product.
+        auto clear_tail = [&](int t) {
+            if (t == n_tiles - 1 && kb + 64 * t + 63 >= ke) {
+#pragma unroll
+                for (int i = 0; i < LW; ++i) {
+                    const int d = ((wave + 8 * i) % KK) * 32 + (lane >> 1), h = (lane & 1) ^ ((d >> 2) & 1);
+                    const int nv = min(max(ke - (kb + 64 * t + 16 * l_page[i] + 8 * h), 0), 8);  // valid tokens of the piece
+                    u32x4* piece = reinterpret_cast<u32x4*>(&Vs[t & 3][l_dst[i] + lane * 8]);
+                    u32x4 bits = *piece;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        bits[w] &= (2 * w < nv ? 0x0000FFFFu : 0u) | (2 * w + 1 < nv ? 0xFFFF0000u : 0u);
+                    *piece = bits;
+                }
+                wait_lgkmcnt0();
+            }
+        };
+
+        f32x4 o[CT][NT], l_acc[CT], sc[4][CT];
+        bf16x8 pf[2][CT];
+        float m_run[CT];
+        int qpos_col[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) o[ct][nt] = f32x4{};
+            l_acc[ct] = f32x4{};
+            m_run[ct] = -INFINITY;
+            qpos_col[ct] = wave_qpos_lo + (ct * 16 + col) / GROUP;
+        }
+
+        // P2 as a chain of fragment groups: the VG groups of four V fragments
+        // of chunk_attn_kernel, then the K fragments of the four score tiles.
+        // Groups are read two ahead of their MFMAs (three register sets),
+        // held in that order by the scheduling groups (0x100: LDS reads, 0x8:
+        // MFMAs); the first two are read at the end of P1.
+        constexpr int VG = 2 * NT / 4, NG = VG + 4, FR = KK > 4 ? KK : 4;
+        bf16x8 fr[3][FR];
+        auto read = [&](int t, int s) {
+            bf16x8(&f)[FR] = fr[s % 3];
+            if (s < VG) {
+                const int j = s / (NT / 4), n0 = (s % (NT / 4)) * 4, v_base = (2 * j + (grp >> 1)) * PAGE;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int d = (n0 + i) * 16 + col;
+                    f[i] = *reinterpret_cast<const bf16x8*>(&Vs[t & 3][v_base + d * 16 + vswz(d, grp & 1) * 8]);
+                }
+            } else {
+                const int p = s - VG, key = pair_key(col, p & 1), tok = key & 15;
+                const int base = (2 * (p >> 1) + (key >> 4)) * PAGE + tok * 32 + kswz(tok, grp) * 8;
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) f[kk] = *reinterpret_cast<const bf16x8*>(&Ks[(t + 1) & 3][base + kk * 512]);
+            }
+        };
+        auto mma = [&](int s) {
+            const bf16x8(&f)[FR] = fr[s % 3];
+            if (s < VG) {
+                const int j = s / (NT / 4), n0 = (s % (NT / 4)) * 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) o[ct][n0 + i] = mfma16(pf[j][ct], f[i], o[ct][n0 + i]);
+                if (n0 == 0) {
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) l_acc[ct] = mfma16(pf[j][ct], ones, l_acc[ct]);
+                }
+            } else {
+                const int p = s - VG;
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) sc[p][ct] = f32x4{};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) sc[p][ct] = mfma16(f[kk], qf[ct][kk], sc[p][ct]);
+            }
+        };
+        // Groups first .. NG - 1, of which two are read, with the loads of
+        // V(t + 3) and K(t + 4) spread between them.
+        auto products = [&](int t, auto first) {
+            constexpr int S0 = decltype(first)::value, N = NG - S0;
+#pragma unroll
+            for (int s = S0; s < NG; ++s) {
+                if (s + 2 < NG) read(t, s + 2);
+                mma(s);
+#pragma unroll
+                for (int l = 0; l < 2 * LW; ++l)
+                    if ((2 * l + 1) * N / (4 * LW) == s - S0) {
+                        if (l < LW) load_v(l, t + 3);
+                        else load_k(l - LW, t + 4);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto softmax = [&](int t) {
+            const int key0 = kb + t * 64;
+            if (key0 + 63 > wave_qpos_lo || key0 + 63 >= ke) {  // the diagonal or the range end
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int kpos = key0 + 32 * (p >> 1) + pair_key(4 * grp + e, p & 1);
+#pragma unroll
+                        for (int ct = 0; ct < CT; ++ct)
+                            sc[p][ct][e] = (kpos <= qpos_col[ct] && kpos < ke) ? sc[p][ct][e] : -INFINITY;
+                    }
+            }
+            float mx[CT];
+            bool grow = false;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                float m = -INFINITY;
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) m = fmaxf(m, sc[p][ct][e]);
+                m = rows4_max(m);
+                mx[ct] = m * sl2;
+                grow |= mx[ct] > m_run[ct] + kSlack;
+            }
+            if (__any(grow)) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    const float m_new = fmaxf(m_run[ct], mx[ct]);
+                    const float alpha = m_new == -INFINITY ? 1.f : fast_exp2(m_run[ct] - m_new);
+                    m_run[ct] = m_new;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float ae = __shfl(alpha, grp * 4 + e, 64);
+                        l_acc[ct][e] *= ae;
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) o[ct][nt][e] *= ae;
+                    }
+                }
+            }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const float m_use = m_run[ct] == -INFINITY ? 0.f : m_run[ct];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sc[p][ct][e] = fast_exp2(fmaf(sc[p][ct][e], sl2, -m_use));
+#pragma unroll
+                for (int j = 0; j < 2; ++j) pf[j][ct] = to_bf16x8(sc[2 * j][ct], sc[2 * j + 1][ct]);
+            }
+        };
+        // The item's Q, K(0 .. 2), V(0) and V(1) before the first slot; the
+        // previous item's buffers are free: its last barrier was passed by
+        // every wave, and no load was left in flight.  Tiles past the end load
+        // the last page into buffers that nobody reads.
+        fetch(0);
+#pragma unroll
+        for (int i = 0; i < LW; ++i) load_k(i, 0);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            next_ids(t + 1);
+#pragma unroll
+            for (int i = 0; i < LW; ++i) {
+                load_v(i, t);
+                load_k(i, t + 1);
+            }
+        }
+        next_ids(3);
+        wait_vmcnt<0>();
+        barrier_only();
+        if (behind) {  // slot 0 of the group behind
+            clear_tail(0);
+            barrier_only();
+        }
+        read(-1, VG);
+        read(-1, VG + 1);
+        products(-1, std::integral_constant<int, VG>{});
+        if (!behind) clear_tail(0);
+        next_ids(4);
+        barrier_only();
+        for (int t = 0; t < n_tiles; ++t) {
+            // P1
+            softmax(t);
+            if (behind) {  // V(t + 1) and K(t + 2) have landed; those of the tile after may not have
+                wait_vmcnt<2 * LW>();
+                clear_tail(t + 1);
+            }
+            read(t, 0);
+            read(t, 1);
+            barrier_only();
+            // P2, ahead of the other wave's softmax at every issue (+2%)
+            __builtin_amdgcn_s_setprio(1);
+            products(t, std::integral_constant<int, 0>{});
+            __builtin_amdgcn_s_setprio(0);
+            if (!behind) {  // the same slot; two tiles' loads are younger
+                wait_vmcnt<4 * LW>();
+                clear_tail(t + 1);
+            }
+            next_ids(t + 5);
+            if (t + 1 == n_tiles) wait_vmcnt<0>();  // nothing in flight into the next item's buffers
+            barrier_only();
+        }
+        if (!behind) barrier_only();
+        if (!wave_live) continue;
+
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            if (!whole) {
+                const size_t rbase = (static_cast<size_t>(item) * a.hkv + kvh) * 256 + wave * 32 + ct * 16;
+                if (grp == 0) a.part_ml[(rbase + col) * 2 + 0] = m_run[ct];
+                if (col == 0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a.part_ml[(rbase + grp * 4 + e) * 2 + 1] = l_acc[ct][e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        a.part_o[(rbase + grp * 4 + e) * HD + nt * 16 + col] = o[ct][nt][e];
+            } else {
+                bf16* out = static_cast<bf16*>(a.out);
+                const int ldo = a.hq * HD;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = ct * 16 + grp * 4 + e;
+                    const int j = j0 + r / GROUP, h = kvh * GROUP + r % GROUP;
+                    const float inv = 1.0f / l_acc[ct][e];
+                    if (j < nrows) {
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+                            out[static_cast<size_t>(row0 + j) * ldo + h * HD + nt * 16 + col] =
+                                f2bf(o[ct][nt][e] * inv);
+                    }
+                }
+            }
+        }
+    }
+}
+
 // Combine n partials (running max, sum and unnormalised output) of one
 // row and write it normalised; 64 threads, HD / 64 dims each.  Partial w
 // sits at row r0 + w * stride of ml [.][2] and po [.][HD]; a max of -inf
@@ -789,13 +1149,15 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_kernel(ChunkAttnArgs ca
 
 template <int HD, int GROUP>
 void launch_chunk_g(const ChunkAttnArgs& a, hipStream_t s) {
-    chunk_attn_kernel<HD, GROUP, kChunkStages, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
+    if (a.pp) chunk_attn_pp_kernel<HD, GROUP, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
+    else chunk_attn_kernel<HD, GROUP, kChunkStages, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
 }
 
 template <int HD, int GROUP>
 void launch_both_g(const ChunkAttnArgs& ca, const DecodeAttnArgs& da, hipStream_t s) {
     const int blocks = ca.n_slots * ca.hkv + (da.n_slots * da.hkv + 7) / 8;
-    chunk_attn_kernel<HD, GROUP, kChunkStages, true><<<blocks, 512, 0, s>>>(ca, da);
+    if (ca.pp) chunk_attn_pp_kernel<HD, GROUP, true><<<blocks, 512, 0, s>>>(ca, da);
+    else chunk_attn_kernel<HD, GROUP, kChunkStages, true><<<blocks, 512, 0, s>>>(ca, da);
 }
 
 template <int HD, int GROUP>

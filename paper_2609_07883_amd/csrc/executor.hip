@@ -42,15 +42,12 @@ constexpr int kChunkMinTiles = 4;
 // Whole query tiles per work-group when the largest group's load is within
 // 11/10 of an equal share.
 constexpr int64_t kChunkWholeSlackNum = 11, kChunkWholeSlackDen = 10;
-// Chunk and decode attention share one launch (decode waves run as chunk
-// work-groups leave CUs free) unless the chunk holds at least this many
-// (query, key) pairs: then decode attention runs on a second stream beside
-// the chunk kernel for its whole length, which a long chunk kernel even
-// finishes sooner (8B layer, 4096-token chunk at a 28 K prefix with eight
-// 16-32 K decodes: 2256 us with the decodes beside it, 2432 us alone).  One
-// launch saves the fork and join, 9-20 us an iteration on the layer sweep's
-// and the chat mix's chunks; the two ways measured even at 8-9 M pairs.
-constexpr int64_t kTwoStreamMinPairs = int64_t{8} << 20;
+// Work-groups that take whole query tiles, or at least this many 64-key tiles
+// each, run the two-phase chunk kernel: below, its extra phases per work item
+// cost more than the overlap gains (8B layer, old / two-phase us: 37 tiles 80
+// / 79, 34 tiles 83 / 82, 29 tiles 66 / 67, 21 tiles 54 / 55; whole tiles 17
+// tiles 58 / 55, 49 tiles 113 / 107, 900 tiles 1670 / 1589).
+constexpr int64_t kTwoPhaseMinTiles = 32;
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -83,6 +80,7 @@ struct ChunkPlan {
     std::vector<int32_t> slot_off;    // [slots + 1] first entry of each work-group in slot_items
     std::vector<int32_t> slot_items;  // [n] the items of each work-group in turn
     std::vector<int32_t> qt_off;      // [n_qt + 1] first item of each query tile
+    int64_t tiles = 0;                // 64-key tiles of all query tiles
     bool whole = false;               // whole query tiles per work-group
 };
 
@@ -108,10 +106,6 @@ struct slw_ctx {
     size_t staging_cap[kRing] = {};
     hipEvent_t staged[kRing] = {};
     int ring = 0;
-    // second stream for decode attention next to a long chunk's attention,
-    // with a fork and a join event per layer
-    hipStream_t side = nullptr;
-    std::vector<hipEvent_t> fork_ev, join_ev;
 
     // stage telemetry: a ring of `stage_depth` event sets, each [layer][stage boundary]
     int stage_depth = 0;
@@ -129,12 +123,6 @@ struct slw_ctx {
             if (staging[i]) (void)hipHostFree(staging[i]);
         }
         for (hipEvent_t e : stage_ev) (void)hipEventDestroy(e);
-        if (side) {
-            (void)hipStreamSynchronize(side);
-            (void)hipStreamDestroy(side);
-        }
-        for (hipEvent_t e : fork_ev) (void)hipEventDestroy(e);
-        for (hipEvent_t e : join_ev) (void)hipEventDestroy(e);
     }
 };
 
@@ -231,24 +219,16 @@ int check_cfg(const slw_model_cfg& c) {
     return SLW_OK;
 }
 
-// The iteration's events order work on this device only: a staging event
+// The staging events order work on this device only: an event
 // tells the host that the set-up kernel has finished reading a pinned buffer
-// (nothing the GPU wrote has to reach the host), and the fork and join
-// events order the two streams' kernels.  Without the system-scope fence an
-// event record does no cache write-back and invalidation (the CUs sat idle
+// (nothing the GPU wrote has to reach the host).  Without the system-scope
+// fence an event record does no cache write-back and invalidation (the CUs sat idle
 // for 6-11 us at each record): 8B-layer sweep +1.4%, chat mix +1.6%.
 constexpr unsigned kSyncEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 
 int ensure_hip(slw_ctx* ctx) {
     if (ctx->hip_ready) return SLW_OK;
     for (int i = 0; i < kRing; ++i) HIP_TRY(hipEventCreateWithFlags(&ctx->staged[i], kSyncEventFlags));
-    HIP_TRY(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
-    ctx->fork_ev.assign(ctx->cfg.n_layers, nullptr);
-    ctx->join_ev.assign(ctx->cfg.n_layers, nullptr);
-    for (int l = 0; l < ctx->cfg.n_layers; ++l) {
-        HIP_TRY(hipEventCreateWithFlags(&ctx->fork_ev[l], kSyncEventFlags));
-        HIP_TRY(hipEventCreateWithFlags(&ctx->join_ev[l], kSyncEventFlags));
-    }
     ctx->hip_ready = true;
     return SLW_OK;
 }
@@ -493,6 +473,7 @@ int plan_chunk(const slw_model_cfg& c, int C, const std::vector<int32_t>& qt_pos
     std::vector<int64_t> tile_end(n_qt + 1, 0);
     for (int q = 0; q < n_qt; ++q) tile_end[q + 1] = tile_end[q] + ceil_div(key_end(q), 64);
     const int64_t total_tiles = tile_end[n_qt];
+    p.tiles = total_tiles;
     std::vector<int32_t>& it = p.items;
     int n_slots = 0;
     if (n_qt > 0) {
@@ -619,8 +600,6 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
     DecodePlan& dp = ctx->dplan;
     if ((rc = plan_decode(c, B, bt->context_lens, dp))) return rc;
     const int n_work = static_cast<int>(dp.b.size()), n_dslots = static_cast<int>(dp.slot_off.size()) - 1;
-    int64_t chunk_pairs = 0;  // (query, key) pairs of the chunk rows: c p + c (c + 1) / 2 per prefill
-    for (const auto& q : pre) chunk_pairs += int64_t{q.c} * q.prefix + int64_t{q.c} * (q.c + 1) / 2;
     m.insert(m.end(), dp.b.begin(), dp.b.end());
     m.insert(m.end(), dp.kb.begin(), dp.kb.end());
     m.insert(m.end(), dp.ke.begin(), dp.ke.end());
@@ -739,8 +718,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
             launch_gemm(ga, plans.qkv, gpartp, stream);
         }
         if ((rc = mark(l, 3))) return rc;
-        // Both attentions in one launch, or on two streams for a long
-        // chunk (see kTwoStreamMinPairs); per-stage events separate them.
+        // Both attentions in one launch; per-stage events separate them.
         ChunkAttnArgs ca{};
         if (C > 0) {
             ca.qkv = qkv;
@@ -769,6 +747,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
             ca.n_items = n_items;
             ca.n_slots = n_slots;
             ca.split = n_items > n_qt ? 1 : 0;
+            ca.pp = cp.whole || cp.tiles >= kTwoPhaseMinTiles * n_slots ? 1 : 0;
         }
         DecodeAttnArgs da{};
         if (B > 0) {
@@ -798,13 +777,6 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
             if (C > 0) launch_chunk_attention(ca, stream);
             if ((rc = mark(l, 4))) return rc;
             if (B > 0) launch_decode_attention_split(da, stream);
-        } else if (C > 0 && B > 0 && !no_alloc && chunk_pairs >= kTwoStreamMinPairs) {
-            HIP_TRY(hipEventRecord(ctx->fork_ev[l], stream));
-            HIP_TRY(hipStreamWaitEvent(ctx->side, ctx->fork_ev[l], 0));
-            launch_chunk_attention(ca, stream);
-            launch_decode_attention_split(da, ctx->side);
-            HIP_TRY(hipEventRecord(ctx->join_ev[l], ctx->side));
-            HIP_TRY(hipStreamWaitEvent(stream, ctx->join_ev[l], 0));
         } else {
             launch_attention(ca, da, stream);
         }

@@ -1,0 +1,60 @@
+"""GPU parity of the two-phase chunk kernel, the one long chunks run, for every
+GQA group size and both head dims: a few query rows over a long cached prefix,
+so that each work-group takes at least 32 key tiles, beside decodes in the same
+launch.  Prefix and chunk end inside a page and inside a 64-key tile, the last
+query tile is ragged, a run of keys crosses query tiles, and every KV slot that
+no token owns holds NaN (values past the range end are cleared in LDS).
+
+Sampled rows against the float64 oracle at the parity bar.
+"""
+import numpy as np
+import pytest
+
+from paper_2609_07883_amd import api, synth
+from paper_2609_07883_amd.synth import ModelShape
+from tests.parity import TOL, Mirror, check
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# (q heads, kv heads, head dim, chunk, prefix)
+CASES = [
+    (16, 16, 64, 300, 16390),
+    (16, 16, 128, 257, 16500),
+    (32, 16, 128, 140, 16500),
+    (32, 8, 128, 200, 16390),
+    (64, 8, 64, 100, 16401),
+    (128, 8, 64, 50, 16383),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"hq{c[0]}_hkv{c[1]}_hd{c[2]}" for c in CASES])
+def test_long_prefix(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_07883_amd.runtime import Session
+    hq, hkv, hd, C, P = case
+    shape = ModelShape(n_layers=1, d_model=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, ffn_dim=256,
+                       rms_eps=1e-5, rope_theta=10000.0, max_pos=32768)
+    dec, ctx = [21, 22], [5, 700]
+    plan = api.attention_plan(shape, ctx, [(P, C)])
+    assert plan["chunk_whole"] or plan["chunk_tiles"] >= 32 * plan["chunk_slots"]
+    qk_std = 0.16 * (64 / hd) ** 0.25
+    sess = Session(shape, num_blocks=(P + C) // 16 + 60, max_c=C, max_b=2, qk_std=qk_std)
+    sess.k_pool.fill_(float("nan"))
+    sess.v_pool.fill_(float("nan"))
+    torch.cuda.synchronize()
+    mir = Mirror(sess, seed=5)
+    for sid, n in [(3, P)] + list(zip(dec, ctx)):
+        mir.create(sid)
+        mir.install_context(sid, n)
+    b = api.Batch(C, 3, P, dec, ctx)
+    x = synth.embeddings(b.rows, shape.d_model, seed=1, stream=C)
+    pw = 256 // (hq // hkv)  # positions of a query tile
+    rows = sorted({r for r in (0, 1, 15, 16, 31, 32, pw - 1, pw, C - 2, C - 1, C, C + 1) if r < b.rows})
+    y, yr, sg, sr = mir.step(b, x, rows=rows)
+    assert sg == sr
+    assert np.isfinite(np.asarray(y, dtype=np.float64)).all()
+    check(y[rows], yr[rows], f"{case}")
+    assert mir.kv_error(b, rows=rows) <= TOL
