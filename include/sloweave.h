@@ -383,9 +383,11 @@ int slw_fill_normal(void* dst, size_t n, uint64_t seed, float mean, float std, v
 /*
  * The GEMM plan an iteration uses for a projection out[m][n] = A[m][k] W^T
  * (host only, touches no GPU), for callers and tests that need to know which
- * kernel variant a row count reaches.  out[0..5]: tile configuration (99:
- * the weight-streaming kernel for m <= 16; 98: the narrow kernel for m <= 24,
- * k split over the waves of a work-group), tile rows BM, tile columns BN, k split factor (1: none), then 0 and 0.
+ * kernel variant a row count reaches.  out[0..5]: tile configuration (99: the
+ * weight-streaming kernel of gate/up, taken to be a projection with n >= 16384,
+ * for m <= 8, which also applies the RMSNorm before it; 98: the narrow kernel
+ * for m <= 24, k split over the waves of a work-group), tile rows BM, tile
+ * columns BN, k split factor (1: none), then 0 and 0.
  * m >= 1; n a multiple of 128 and k of 64, else SLW_EINVAL.
  */
 int slw_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t out[6]);

@@ -196,9 +196,10 @@ struct LayerPlans {
 };
 
 LayerPlans plan_layer(const slw_model_cfg& c, int M, int max_splits = kMaxSplits) {
-    return {plan_gemm(M, qkv_width(c), c.d_model, max_splits),
-            plan_gemm(M, c.d_model, c.n_q_heads * c.head_dim, max_splits),
-            plan_gemm(M, 2 * c.ffn_dim, c.d_model, max_splits), plan_gemm(M, c.d_model, c.ffn_dim, max_splits)};
+    return {plan_gemm(M, qkv_width(c), c.d_model, false, max_splits),
+            plan_gemm(M, c.d_model, c.n_q_heads * c.head_dim, false, max_splits),
+            plan_gemm(M, 2 * c.ffn_dim, c.d_model, true, max_splits),
+            plan_gemm(M, c.d_model, c.ffn_dim, false, max_splits)};
 }
 
 int check_cfg(const slw_model_cfg& c) {
@@ -786,9 +787,17 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         launch_gemm(GemmArgs{attn, wl.wo, hbuf, cur, M, d, hq * hd, hq * hd, d, EPI_RESID_F32OUT}, plans.o, gpartp,
                     stream);
         if ((rc = mark(l, 7))) return rc;
-        launch_rmsnorm(hbuf, true, wl.g2, xn, M, d, c.rms_eps, stream);
+        const bool gu_norm = plans.gu.cfg == kStreamCfg;  // that kernel normalises its rows itself
+        if (!gu_norm) launch_rmsnorm(hbuf, true, wl.g2, xn, M, d, c.rms_eps, stream);
         if ((rc = mark(l, 8))) return rc;
-        launch_gemm(GemmArgs{xn, wl.wgu, act, nullptr, M, 2 * F, d, d, F, EPI_SWIGLU}, plans.gu, gpartp, stream);
+        {
+            GemmArgs ga{gu_norm ? hbuf : xn, wl.wgu, act, nullptr, M, 2 * F, d, d, F, EPI_SWIGLU};
+            if (gu_norm) {
+                ga.norm_g = wl.g2;
+                ga.norm_eps = c.rms_eps;
+            }
+            launch_gemm(ga, plans.gu, gpartp, stream);
+        }
         if ((rc = mark(l, 9))) return rc;
         launch_gemm(GemmArgs{act, wl.wd, x_out, hbuf, M, d, F, F, d, EPI_RESID_F32IN}, plans.d, gpartp, stream);
         if ((rc = mark(l, 10))) return rc;
@@ -891,7 +900,7 @@ extern "C" int slw_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t out[6]) {
     if (!out) return fail(SLW_EINVAL, "null argument");
     if (m < 1 || n < 128 || n % 128 || k < 64 || k % 64)
         return fail(SLW_EINVAL, "m >= 1, n a multiple of 128 and k of 64 (got %d, %d, %d)", m, n, k);
-    const GemmPlan p = plan_gemm(m, n, k);
+    const GemmPlan p = plan_gemm(m, n, k, true);
     const int32_t v[6] = {p.cfg, p.bm, p.bn, p.splits, 0, 0};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
     return SLW_OK;

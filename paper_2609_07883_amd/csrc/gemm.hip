@@ -584,155 +584,123 @@ __device__ __forceinline__ int w_row(const GemmArgs& g, int c) {
     return c;
 }
 
-// Weight-streaming GEMM for wide projections (gate/up) of at most 16 rows.  W is read once,
-// straight from memory into MFMA operand registers with no LDS staging, so
-// the bytes in flight per CU are bounded only by registers and occupancy.
-// A work-group has KS waves that split its k range; every wave computes the
-// same 64 B columns (two 32-column groups that pair like the tile kernel's
-// epilogue tiles) for all tokens over its k slice, and the slices are summed
-// through LDS before the epilogue.  Work-groups are small so that several
-// share a CU and the whole grid runs in one round.
-// In a 64-wide k step a lane reads 64 contiguous bytes of its row (lanes
-// 0-31 the first 32 k, lanes 32-63 the next 32); the step's four MFMAs take
-// its 16-byte quarters.  Both operands use this same order of k inside the
-// step, so every dot product is unchanged.  MFMA rows are W rows and columns
-// are tokens: element e of lane l is W row 8(e/4) + 4(l/32) + e%4 of its
-// column group, token 32 t + l%32.
-template <int EPI>
-__global__ __launch_bounds__(256) void skinny_kernel(GemmArgs g, int ks_count) {
-    constexpr int T = 1;
-    constexpr int NA = 2 * T;  // accumulator tiles: 2 column groups x T token groups
-    __shared__ float red[2][NA * 16][64];  // ks_count / 2 <= 2 slots
+// ---------------------------------------------------------------------------
+// Weight-streaming gate/up GEMM for up to 8 rows, with the RMSNorm before it
+// folded in.
+//
+// Bound by the weights' way from HBM: a CU draws about 23 KB/us, so all 256
+// have to draw evenly and without a pause.  A work-group of eight waves takes
+// a run of units of 16 W rows (eight gate rows and their up rows) one after the
+// other, each wave an eighth of k; its loads run R slices of 32 k ahead (1 KB
+// each) across unit boundaries, so the stream never drains.  The wave's
+// activations for all rows stay in registers (they are the same for every
+// unit); a unit's eight partial sums meet in one of two LDS buffers, and the
+// waves take turns to add them and store, while the others stream on.
+//
+// g.a holds the rows before the RMSNorm in fp32, and each work-group
+// normalises them itself while its first weights are on their way: the same
+// arithmetic as the RMSNorm kernel, whose launch (4 us) is saved.  Every
+// work-group reads all rows, which is what limits it to few of them.
+//
+// 8B layer, norm included, against the RMSNorm kernel and a weight-streaming
+// kernel of 448 work-groups: 50.1 -> 46 us at 1 row (235 MB: 5.1 TB/s), 52.9 ->
+// 50 at 8; at 16 rows 58 against 49 for RMSNorm and the tile kernel.  The same
+// for the qkv projection lost at every row count (19.5 against 18.9 us at 1 row,
+// 24 against 21 at 8): two units a CU do not pay for the rows' read.
+// ---------------------------------------------------------------------------
+constexpr int kStreamMaxRows = 8;
+// slices in flight per wave, a divisor of the slices of a unit
+constexpr int stream_ring(int ns) { return ns % 8 == 0 ? 8 : ns % 10 == 0 ? 10 : 6; }
+// k = 256 NS; beyond 6144 the rows no longer fit the registers
+constexpr bool stream_k_ok(int k) { return k % 1024 == 0 && k >= 2048 && k <= 6144; }
 
-    const int lane = threadIdx.x & 63, ks = threadIdx.x >> 6;
-    const int r = lane & 31, h = lane >> 5;
-    const int c0 = blockIdx.x * 64;
-    const int k_wave = g.k / ks_count;
-    const int kbeg = ks * k_wave + 32 * h;
-    const int nkb = k_wave / 64;
-
-    const bf16* W = static_cast<const bf16*>(g.w);
-    const bf16* A = static_cast<const bf16*>(g.a);
-    const bf16* wp[2];
-    wp[0] = W + static_cast<size_t>(w_row<EPI>(g, c0 + r)) * g.k + kbeg;
-    wp[1] = W + static_cast<size_t>(w_row<EPI>(g, c0 + 32 + r)) * g.k + kbeg;
-    const bf16* ap[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t)  // rows past m read row m-1; their results are never stored
-        ap[t] = A + static_cast<size_t>(min(t * 32 + r, g.m - 1)) * g.lda + kbeg;
-
-    bf16x8 wf[2][2][4], af[2][T][4];
-    auto load = [&](int kb, int b) {
-        const int off = kb * 64;
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) wf[b][c][j] = *reinterpret_cast<const bf16x8*>(wp[c] + off + 8 * j);
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) af[b][t][j] = *reinterpret_cast<const bf16x8*>(ap[t] + off + 8 * j);
+template <int NS>
+__global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, int per_wg) {
+    constexpr int R = stream_ring(NS);
+    static_assert(NS % R == 0, "a unit is whole turns of the ring");
+    __shared__ f32x4 red[2][8][64];
+    __shared__ float ssq[8][16];
+    const int lane = threadIdx.x & 63, ks = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int j = lane & 15, grp = lane >> 4;
+    const int u0 = blockIdx.x * per_wg, u1 = min(u0 + per_wg, units);
+    const int kbeg = ks * NS * 32 + 8 * grp;
+    // W row of this lane in unit u: rows 0 .. 7 of the MFMA take gate rows 8 u .. 8 u + 7, rows 8 .. 15 their up rows
+    auto wptr = [&](int u) {
+        const int row = 8 * u + (j & 7) + (j >> 3) * (g.n >> 1);
+        return static_cast<const bf16*>(g.w) + static_cast<size_t>(row) * g.k + kbeg;
     };
-    f32x16 acc[2][T];
+    bf16x8 wf[R];
+    const bf16* wp = wptr(u0);
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int s = 0; s < R; ++s) wf[s] = *reinterpret_cast<const bf16x8*>(wp + 32 * s);
+
+    // activations: row j (rows past m repeat row m - 1; their results are never
+    // stored), read once and normalised in registers
+    bf16x8 af[NS];
+    {
+        const size_t arow = static_cast<size_t>(min(j, g.m - 1)) * g.lda + kbeg;
+        f32x4 raw[NS][2];
+        float ss = 0.f;
 #pragma unroll
-        for (int t = 0; t < T; ++t) acc[c][t] = f32x16{};
-    auto compute = [&](int b) {
+        for (int s = 0; s < NS; ++s) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(static_cast<const float*>(g.a) + arow + 32 * s);
+            raw[s][0] = src[0];
+            raw[s][1] = src[1];
+        }
+        auto x = [&](int s, int e) { return raw[s][e / 4][e % 4]; };
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int e = 0; e < 8; ++e) ss += x(s, e) * x(s, e);
+        ss += __shfl_xor(ss, 16, 64);
+        ss += __shfl_xor(ss, 32, 64);
+        if (grp == 0) ssq[ks][j] = ss;
+        wait_lgkmcnt<0>();
+        barrier_only();
+        float tot = 0.f;
 #pragma unroll
-                for (int t = 0; t < T; ++t) acc[c][t] = mfma32(wf[b][c][j], af[b][t][j], acc[c][t]);
+        for (int w = 0; w < 8; ++w) tot += ssq[w][j];
+        const float inv = 1.0f / sqrtf(tot / static_cast<float>(g.k) + g.norm_eps);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const bf16x8 gain = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(g.norm_g) + kbeg + 32 * s);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) af[s][e] = f2bf(x(s, e) * inv * bf2f(gain[e]));
+        }
+    }
+
+    // One unit; with MORE, the loads of the next one follow on.
+    auto unit = [&](int u, auto more_c) {
+        constexpr bool MORE = decltype(more_c)::value;
+        const bf16* wn = MORE ? wptr(u + 1) : nullptr;
+        f32x4 acc = {};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            acc = mfma16(wf[s % R], af[s], acc);
+            if (s + R < NS) wf[s % R] = *reinterpret_cast<const bf16x8*>(wp + 32 * (s + R));
+            else if (MORE) wf[s % R] = *reinterpret_cast<const bf16x8*>(wn + 32 * (s + R - NS));
+        }
+        wp = wn;
+        const int b = (u - u0) & 1;
+        red[b][ks][lane] = acc;
+        // no wait for the loads in flight: only the sums have to be there
+        wait_lgkmcnt<0>();
+        barrier_only();
+        if (((u - u0) & 7) != ks) return;
+        f32x4 v = red[b][0][lane];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) v += red[b][w][lane];
+        // lane groups 0, 1 hold the gates of outputs 8 u + 4 grp + e of row j, the lanes 32 on their ups
+        f32x4 up;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) up[e] = __shfl_xor(v[e], 32, 64);
+        if (grp >= 2 || j >= g.m) return;
+        const bf16 o[4] = {f2bf(silu(v[0]) * up[0]), f2bf(silu(v[1]) * up[1]), f2bf(silu(v[2]) * up[2]),
+                           f2bf(silu(v[3]) * up[3])};
+        store_bf16<4>(static_cast<bf16*>(g.out) + static_cast<size_t>(j) * g.ldo + 8 * u + 4 * grp, o);
     };
-
-    load(0, 0);
-    for (int kb = 0; kb < nkb; kb += 2) {
-        if (kb + 1 < nkb) load(kb + 1, 1);
-        compute(0);
-        if (kb + 1 >= nkb) break;
-        if (kb + 2 < nkb) load(kb + 2, 0);
-        compute(1);
-    }
-
-    // Sum the k slices: halve the active slices per round.
-    for (int half = ks_count / 2; half >= 1; half /= 2) {
-        if (ks >= half && ks < 2 * half) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) red[ks - half][(c * T + t) * 16 + e][lane] = acc[c][t][e];
-        }
-        __syncthreads();
-        if (ks < half) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[c][t][e] += red[ks][(c * T + t) * 16 + e][lane];
-        }
-        __syncthreads();
-    }
-    if (ks != 0) return;
-
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int row = t * 32 + r;
-        if (row >= g.m) continue;
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            const int i0 = 8 * e4 + 4 * h;  // W row of element 4 e4 within its column group
-            if (EPI == EPI_QKV) {
-                // rotations (and the KV slot) read before any store, which the
-                // compiler cannot tell apart from the tables
-                const int hg = c0 / g.hd, d0 = ((c0 % g.hd) / 64) * 32 + i0;
-                const bool rot = hg < g.hq + g.hkv;
-                float2 cs[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    cs[q] = rot ? g.rope_cs[row * (g.hd / 2) + d0 + q] : make_float2(1.f, 0.f);
-                const int slot = hg < g.hq ? 0 : g.slot[row];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    qkv_store_cs(g, row, hg, d0 + q, acc[0][t][4 * e4 + q], acc[1][t][4 * e4 + q], cs[q], slot);
-            } else if (EPI == EPI_SWIGLU) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    static_cast<bf16*>(g.out)[static_cast<size_t>(row) * g.ldo + (c0 >> 1) + i0 + q] =
-                        f2bf(silu(acc[0][t][4 * e4 + q]) * acc[1][t][4 * e4 + q]);
-            } else {
-                // four consecutive output columns per lane: one vector read of
-                // the residual and one vector store for each 32-column group
-                f32x4 rv[2];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const size_t o = static_cast<size_t>(row) * g.ldo + c0 + 32 * c + i0;
-                    if (EPI == EPI_RESID_F32OUT) {
-                        const bf16x4 rb = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(g.resid) + o);
-                        rv[c] = f32x4{bf2f(rb[0]), bf2f(rb[1]), bf2f(rb[2]), bf2f(rb[3])};
-                    } else {
-                        rv[c] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.resid) + o);
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const size_t o = static_cast<size_t>(row) * g.ldo + c0 + 32 * c + i0;
-                    const f32x4 v = f32x4{acc[c][t][4 * e4], acc[c][t][4 * e4 + 1], acc[c][t][4 * e4 + 2],
-                                          acc[c][t][4 * e4 + 3]} + rv[c];
-                    if (EPI == EPI_RESID_F32OUT) {
-                        *reinterpret_cast<f32x4*>(static_cast<float*>(g.out) + o) = v;
-                    } else {
-                        const bf16x4 ob = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-                        *reinterpret_cast<bf16x4*>(static_cast<bf16*>(g.out) + o) = ob;
-                    }
-                }
-            }
-        }
-    }
+    for (int u = u0; u + 1 < u1; ++u) unit(u, std::integral_constant<bool, true>{});
+    unit(u1 - 1, std::integral_constant<bool, false>{});
 }
 
 // Narrow GEMM for m <= 32 rows (decode-sized batches): a work-group of KS
@@ -880,6 +848,22 @@ void launch_cfg(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t
     }
 }
 
+template <int NS>
+void launch_stream_ns(const GemmArgs& g, hipStream_t s) {
+    const int units = g.n / 16, per = (units + kCus - 1) / kCus;
+    stream_kernel<NS><<<(units + per - 1) / per, 512, 0, s>>>(g, units, per);
+}
+
+void launch_stream(const GemmArgs& g, hipStream_t s) {
+    switch (g.k / 1024) {  // stream_k_ok
+        case 2: launch_stream_ns<8>(g, s); break;
+        case 3: launch_stream_ns<12>(g, s); break;
+        case 4: launch_stream_ns<16>(g, s); break;
+        case 5: launch_stream_ns<20>(g, s); break;
+        default: launch_stream_ns<24>(g, s); break;
+    }
+}
+
 template <int T, int CG, int EPI>
 void launch_narrow_epi(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     narrow_kernel<T, CG, EPI><<<g.n / (16 * CG), 64 * p.ks, 0, s>>>(g, p.ks);
@@ -928,9 +912,8 @@ float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
 
 }  // namespace
 
-// Wide projections (gate/up) of up to 16 rows take the weight-streaming
-// kernel: 46 / 48 / 51 us at 1 / 8 / 16 rows of the 8B layer against 49 / 49 /
-// 49 for the tile kernel, which is ahead from there on (51 against 59 at 24).
+// Wide gate/up projections of up to 8 rows take the weight-streaming kernel with
+// the norm folded in, where k is one it is built for.
 // The narrow kernel takes qkv- and down-like projections up to 8 rows and the
 // output projection up to 24 (8B layer, against the tile kernel, us at 1 / 8 /
 // 24 rows: output 8.4 / 9.2 / 12.4 against 11.6 / 12.1 / 12.4; down 21.6 /
@@ -939,10 +922,10 @@ float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
 // counts, where each of its work-groups re-reads all activation rows, take the tile kernel with the configuration and split that
 // predict_us ranks first.  n must be a multiple of 128 and k of 64; a split
 // keeps at least 512 of k.
-GemmPlan plan_gemm(int m, int n, int k, int max_splits) {
+GemmPlan plan_gemm(int m, int n, int k, bool swiglu, int max_splits) {
     const bool wide = n >= 16384, qkv_like = n >= 6144 && !wide;
+    if (swiglu && wide && m <= kStreamMaxRows && stream_k_ok(k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
     if (!wide && (m <= 8 || (m <= 24 && !qkv_like && k < 8192))) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
-    if (wide && m <= 16) return plan_with_cfg(kSkinnyCfg, 1, m, n, k);
     int cfg = kNumCfgs - 1, splits = 1;
     const int m32 = (m + 31) / 32 * 32;
     float best = 0.f;
@@ -973,12 +956,9 @@ GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k) {
         p.bn = 16;
         return p;
     }
-    if (cfg == kSkinnyCfg) {  // four waves slice k (fewer when k is short), whole 64-wide steps each
-        int ks = 4;
-        while (ks > 1 && k % (64 * ks)) ks /= 2;
-        p.ks = ks;
-        p.bm = 32;
-        p.bn = 64;
+    if (cfg == kStreamCfg) {
+        p.bm = kStreamMaxRows;
+        p.bn = 16;
         return p;
     }
     p.bm = kCfgs[cfg].bm;
@@ -991,7 +971,7 @@ GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k) {
 bool gemm_shape_ok(const GemmPlan& p, int n, int k) {
     if (p.cfg == kNarrowCfg)  // m <= 32 is the caller's part; paired epilogues need 64-column tiles
         return n % 64 == 0 && p.ks >= 1 && p.ks <= 8 && k % (32 * p.ks) == 0;
-    if (p.cfg == kSkinnyCfg) return n % 64 == 0 && p.ks >= 1 && p.ks <= 4 && k % (64 * p.ks) == 0;
+    if (p.cfg == kStreamCfg) return n % 16 == 0 && stream_k_ok(k);  // m <= 8 and the SwiGLU epilogue are the caller's part
     return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 
@@ -1002,14 +982,8 @@ void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_
         else launch_narrow<2>(g, p, s);
         return;
     }
-    if (p.cfg == kSkinnyCfg) {
-        const dim3 grid(g.n / 64);
-        switch (g.epi) {
-            case EPI_RESID_F32OUT: skinny_kernel<EPI_RESID_F32OUT><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
-            case EPI_RESID_F32IN: skinny_kernel<EPI_RESID_F32IN><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
-            case EPI_SWIGLU: skinny_kernel<EPI_SWIGLU><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
-            default: skinny_kernel<EPI_QKV><<<grid, 64 * p.ks, 0, s>>>(g, p.ks); break;
-        }
+    if (p.cfg == kStreamCfg) {
+        launch_stream(g, s);
         return;
     }
     switch (p.cfg) {  // kCfgs order

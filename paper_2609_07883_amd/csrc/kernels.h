@@ -34,18 +34,23 @@ struct GemmArgs {
     void* k_pool;           // this layer's pages
     void* v_pool;
     int hq, hkv, hd;
+    // kStreamCfg only: a holds the rows before the RMSNorm with these gains, in
+    // fp32, and the kernel applies it
+    const void* norm_g = nullptr;
+    float norm_eps = 0.f;
 };
 struct GemmPlan {
-    int cfg;      // tile configuration index (kSkinnyCfg, kNarrowCfg: the streaming kernels)
+    int cfg;      // tile configuration index (kStreamCfg, kNarrowCfg: the streaming kernels)
     int bm, bn;
     int splits;   // split-K factor across work-groups (1: fused epilogue)
     size_t partial_bytes;
-    int ks;       // streaming kernels: waves that share the k range of a work-group
+    int ks;       // narrow kernel: waves that share the k range of a work-group
 };
-constexpr int kSkinnyCfg = 99;  // the weight-streaming kernel (m <= 16)
+constexpr int kStreamCfg = 99;  // the weight-streaming kernel (gate/up, m <= 8), which takes unnormalised rows
 constexpr int kNarrowCfg = 98;  // the narrow kernel (m <= 32, k split inside the work-group)
 constexpr int kMaxSplits = 8;
-GemmPlan plan_gemm(int m, int n, int k, int max_splits = kMaxSplits);
+// swiglu: the gate/up projection
+GemmPlan plan_gemm(int m, int n, int k, bool swiglu, int max_splits = kMaxSplits);
 // The plan for a given configuration and k split.
 GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k);
 // Whether the plan's tiles divide n and its splits k.
