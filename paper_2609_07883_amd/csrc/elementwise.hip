@@ -30,10 +30,8 @@ struct Vec8<float> {
 
 // One work-group per row, 8 values per access, fp32 arithmetic; d <= 8192.
 template <typename T>
-__global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const T* __restrict__ x,
-                                                               const bf16* __restrict__ g,
-                                                               bf16* __restrict__ y, int d, float eps) {
-    const int row = blockIdx.x;
+__device__ __forceinline__ void rmsnorm_row(const T* __restrict__ x, const bf16* __restrict__ g, bf16* __restrict__ y,
+                                            int row, int d, float eps) {
     const T* xr = x + static_cast<size_t>(row) * d;
     const bf16x8* gv = reinterpret_cast<const bf16x8*>(g);
     bf16x8* yr = reinterpret_cast<bf16x8*>(y + static_cast<size_t>(row) * d);
@@ -70,6 +68,13 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const T* __restri
     }
 }
 
+template <typename T>
+__global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const T* __restrict__ x,
+                                                               const bf16* __restrict__ g,
+                                                               bf16* __restrict__ y, int d, float eps) {
+    rmsnorm_row(x, g, y, blockIdx.x, d, eps);
+}
+
 // One thread per (row, frequency): cos and sin of position pos[r] times
 // theta^(-i/half), formed in fp64 so that large positions keep their accuracy.
 __device__ __forceinline__ void rope_entry(const int32_t* pos, float2* cs, int idx, int half, double theta) {
@@ -99,11 +104,15 @@ __global__ void sweep_kernel(uint32_t* p, size_t n4, uint32_t key) {
 // (one 16-byte read per thread over the bus, then a tail of single words);
 // done by a kernel rather than the copy engine, the copy is ordered with the
 // kernels around it on the stream without a hand-off between engines.  The
-// other blocks fill the RoPE table, reading the positions from the host copy
-// (the device copy is not complete while this kernel runs).
-__global__ void iteration_setup_kernel(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, size_t n,
-                                       unsigned copy_blocks, const int32_t* __restrict__ pos_host,
-                                       float2* __restrict__ cs, int rows, int half, double theta) {
+// next rope_blocks fill the RoPE table, reading the positions from the host
+// copy (the device copy is not complete while this kernel runs).  The others
+// normalise the first layer's rows, one each: as a launch of its own that
+// RMSNorm cost 3-4 us of every iteration, most of it spent starting up behind
+// this kernel, which itself waits on the bus.
+__global__ __launch_bounds__(kNormThreads) void iteration_setup_kernel(
+    uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, size_t n, unsigned copy_blocks, unsigned rope_blocks,
+    const int32_t* __restrict__ pos_host, float2* __restrict__ cs, int rows, int half, double theta,
+    const bf16* __restrict__ x, const bf16* __restrict__ gain, bf16* __restrict__ xn, int d, float eps) {
     if (blockIdx.x < copy_blocks) {
         const size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
         const size_t n4 = n / 4;
@@ -115,8 +124,12 @@ __global__ void iteration_setup_kernel(uint32_t* __restrict__ dst, const uint32_
         }
         return;
     }
-    const int idx = static_cast<int>(blockIdx.x - copy_blocks) * blockDim.x + threadIdx.x;
-    if (idx < rows * half) rope_entry(pos_host, cs, idx, half, theta);
+    if (blockIdx.x < copy_blocks + rope_blocks) {
+        const int idx = static_cast<int>(blockIdx.x - copy_blocks) * blockDim.x + threadIdx.x;
+        if (idx < rows * half) rope_entry(pos_host, cs, idx, half, theta);
+        return;
+    }
+    rmsnorm_row(x, gain, xn, static_cast<int>(blockIdx.x - copy_blocks - rope_blocks), d, eps);
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC 2011): a counter-based
@@ -172,15 +185,18 @@ void launch_fill_normal(void* dst, size_t n, uint64_t seed, float mean, float st
 }
 
 void launch_iteration_setup(void* dst, const void* src, size_t words, const int32_t* pos_host, float2* cs,
-                            int rows, int hd, double theta, hipStream_t s) {
+                            int rows, int hd, double theta, const void* x, const void* gain, void* xn, int d,
+                            float eps, hipStream_t s) {
     const size_t copy_threads = words / 4 + (words & 3);
-    const unsigned copy_blocks = static_cast<unsigned>((copy_threads + 255) / 256);
+    const unsigned copy_blocks = static_cast<unsigned>((copy_threads + kNormThreads - 1) / kNormThreads);
     const int half = hd / 2;
-    const unsigned rope_blocks = static_cast<unsigned>((static_cast<size_t>(rows) * half + 255) / 256);
-    if (copy_blocks + rope_blocks == 0) return;
-    iteration_setup_kernel<<<copy_blocks + rope_blocks, 256, 0, s>>>(
-        static_cast<uint32_t*>(dst), static_cast<const uint32_t*>(src), words, copy_blocks, pos_host, cs, rows,
-        half, theta);
+    const unsigned rope_blocks =
+        static_cast<unsigned>((static_cast<size_t>(rows) * half + kNormThreads - 1) / kNormThreads);
+    const unsigned norm_blocks = x ? static_cast<unsigned>(rows) : 0;
+    if (copy_blocks + rope_blocks + norm_blocks == 0) return;
+    iteration_setup_kernel<<<copy_blocks + rope_blocks + norm_blocks, kNormThreads, 0, s>>>(
+        static_cast<uint32_t*>(dst), static_cast<const uint32_t*>(src), words, copy_blocks, rope_blocks, pos_host, cs,
+        rows, half, theta, static_cast<const bf16*>(x), static_cast<const bf16*>(gain), static_cast<bf16*>(xn), d, eps);
 }
 
 void launch_rmsnorm(const void* x, bool x_f32, const void* g, void* y, int rows, int d, float eps,

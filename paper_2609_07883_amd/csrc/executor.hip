@@ -646,6 +646,10 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
     if (m.size() > meta_ints(c, C, B)) return fail(SLW_EINVAL, "internal: metadata %zu ints above its region", m.size());
 
     // ---- upload ----
+    const bool timing = !no_alloc && ctx->stage_depth > 0;
+    // the first layer's RMSNorm runs in the setup kernel, or, where stages are
+    // timed, as a stage of its own
+    const void* setup_x = timing ? nullptr : x_in;
     char* wsb = static_cast<char*>(ws);
     int32_t* dmeta = reinterpret_cast<int32_t*>(wsb + L.meta);
     float2* rope = reinterpret_cast<float2*>(wsb + L.rope);
@@ -656,7 +660,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         HIP_TRY(hipMemcpyAsync(dmeta, m.data(), m.size() * 4, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         launch_iteration_setup(dmeta, nullptr, 0, dmeta + M, rope, M, c.head_dim, static_cast<double>(c.rope_theta),
-                               stream);
+                               setup_x, ctx->w[0].g1, wsb + L.xn, c.d_model, c.rms_eps, stream);
         HIP_TRY(hipGetLastError());
     } else {
         int32_t* stage = nullptr;
@@ -664,9 +668,10 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         rc = next_staging(ctx, m.size(), &stage, &slot);
         if (rc) return rc;
         std::memcpy(stage, m.data(), m.size() * 4);
-        // metadata copy and RoPE table (positions follow the M slots) in one kernel
+        // metadata copy, RoPE table (positions follow the M slots) and the first RMSNorm in one kernel
         launch_iteration_setup(dmeta, ctx->staging_dev[slot], m.size(), ctx->staging_dev[slot] + M, rope, M,
-                               c.head_dim, static_cast<double>(c.rope_theta), stream);
+                               c.head_dim, static_cast<double>(c.rope_theta), setup_x, ctx->w[0].g1, wsb + L.xn,
+                               c.d_model, c.rms_eps, stream);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipEventRecord(ctx->staged[slot], stream));
     }
@@ -683,7 +688,6 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
     const int qw = qkv_width(c);
     const size_t layer_pool = static_cast<size_t>(ctx->kv.num_blocks()) * hkv * hd * 16 * 2;
 
-    const bool timing = !no_alloc && ctx->stage_depth > 0;
     size_t set_base = 0;
     int set = 0;
     if (timing) {
@@ -704,7 +708,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         void* vp = static_cast<char*>(ctx->v_pool) + l * layer_pool;
 
         if ((rc = mark(l, 0))) return rc;
-        launch_rmsnorm(cur, false, wl.g1, xn, M, d, c.rms_eps, stream);
+        if (l > 0 || !setup_x) launch_rmsnorm(cur, false, wl.g1, xn, M, d, c.rms_eps, stream);
         if ((rc = mark(l, 1))) return rc;  // the RoPE table stage is empty: the setup kernel fills the table
         if ((rc = mark(l, 2))) return rc;
         {

@@ -119,11 +119,14 @@ void launch_attention(const ChunkAttnArgs& ca, const DecodeAttnArgs& da, hipStre
 void launch_attention_merge(const ChunkAttnArgs* ca, const DecodeAttnArgs* da, hipStream_t s);
 
 // One kernel: copy `words` 32-bit words from coherent, mapped host memory
-// (its device address; both pointers 16-byte aligned) to device memory, and
-// fill the RoPE table: cs[r][i] = (cos, sin) of pos_host[r] * theta^(-2i/hd),
-// i < hd/2, formed in double (pos_host lies in that host memory).
+// (its device address; both pointers 16-byte aligned) to device memory, fill
+// the RoPE table: cs[r][i] = (cos, sin) of pos_host[r] * theta^(-2i/hd),
+// i < hd/2, formed in double (pos_host lies in that host memory), and
+// normalise the first layer's rows x [rows][d] (bf16; may be null: not done)
+// with its gains into xn.
 void launch_iteration_setup(void* dst, const void* src, size_t words, const int32_t* pos_host, float2* cs,
-                            int rows, int hd, double theta, hipStream_t s);
+                            int rows, int hd, double theta, const void* x, const void* gain, void* xn, int d,
+                            float eps, hipStream_t s);
 
 // dst[i] = bf16(mean + std z_i), z the standard normals of the Philox4x32-10
 // stream keyed by seed (element i from draw i / 4 by Box-Muller).
