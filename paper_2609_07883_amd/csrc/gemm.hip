@@ -1,17 +1,19 @@
 // bf16 GEMM out = A W^T on gfx950 matrix cores, with fused epilogues.
 //
-// A [m][k] and W [n][k] are both k-contiguous.  Two kernels:
+// A [m][k] and W [n][k] are both k-contiguous.  Three kernels:
 //   tile_kernel    BM x BN output tiles staged through LDS, for everything
 //                  but the smallest batches; k may be split across
 //                  work-groups, whose fp32 partial sums a second kernel adds
 //                  before it applies the same epilogue;
-//   narrow_kernel  weight streaming for a few rows, k split over the waves of
-//                  one work-group.
+//   stream_kernel  weight streaming of wide gate/up projections for up to 8
+//                  rows, with the RMSNorm before them folded in;
+//   narrow_kernel  weight streaming of the other projections for a few rows,
+//                  k split over the waves of one work-group.
 //
 // Two epilogues need two W rows of one output in the same lane: SwiGLU (a gate
 // row and its up row) and QKV (dims i and i + hd/2 of a head, a RoPE pair).
-// Both kernels choose which W rows feed which MFMA rows so that the two sit
-// in one lane at the same element of two accumulators.
+// The kernels choose which W rows feed which MFMA rows so that the two sit in
+// one lane (stream_kernel: in lanes 32 apart).
 #include <math.h>
 
 #include <algorithm>
