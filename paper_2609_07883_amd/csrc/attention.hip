@@ -527,14 +527,16 @@ __global__ __launch_bounds__(512) void chunk_attn_kernel(ChunkAttnArgs a, Decode
 // start, and waves 0-3 one at its end), so that on every SIMD one wave's
 // softmax runs under the other's products, with one copy of the code and no
 // register held across phases that the plain order would not hold.  Every wave
-// computes every tile of its item, masked where the tile lies past its rows:
-// branches around the phases cost 83 spilled registers.
+// computes every tile of its item (branches around the phases cost 83 spilled
+// registers); where the tile lies past its rows, its scores are masked and its
+// values read from a tile of zeros, so that a non-finite value row of a later
+// token stays out of the products (0 times it would be NaN).
 //
 // One wave per SIMD must keep the matrix cores fed in P2, so its LDS reads run
 // two fragment groups ahead, the first two already in P1, and its direct loads
 // are spread between the groups (issued together they hold up the MFMAs behind
 // them: 1790 -> 1624 us with the next point).  K and V have rings of four
-// 16 KB tiles (128 KB).  In slots (phases of waves 0-3), P2(t) of the two
+// 16 KB tiles (144 KB with the zeros).  In slots (phases of waves 0-3), P2(t) of the two
 // groups, slots 2t + 2 and 2t + 3, reads V(t) and K(t + 1) and loads V(t + 3)
 // and K(t + 4) into the buffers of V(t - 1) and K(t), last read in slot 2t + 1;
 // V(t + 1) and K(t + 2) are published by the barrier that ends slot 2t + 2, one
@@ -564,7 +566,7 @@ __global__ __launch_bounds__(512) void chunk_attn_pp_kernel(ChunkAttnArgs a, Dec
     constexpr int PW = 32 / GROUP;      // positions per wave
     constexpr float kSlack = 8.0f;      // lazy rescaling threshold, as in chunk_attn_kernel
     __shared__ __attribute__((aligned(16))) bf16 Ks[4][4 * PAGE];
-    __shared__ __attribute__((aligned(16))) bf16 Vs[4][4 * PAGE];
+    __shared__ __attribute__((aligned(16))) bf16 Vs[5][4 * PAGE];  // the last one: zeros
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int behind = wave >> 2;  // 1: the group that runs one phase behind
@@ -591,6 +593,9 @@ __global__ __launch_bounds__(512) void chunk_attn_pp_kernel(ChunkAttnArgs a, Dec
         l_v[i] = d * 16 + h * 8;
         l_dst[i] = p * PAGE + slab * 512;
     }
+    // visible to every wave from the barrier before the first item's first phase
+    for (int e = tid; e < 4 * PAGE / 8; e += 512) *reinterpret_cast<u32x4*>(&Vs[4][e * 8]) = u32x4{};
+    wait_lgkmcnt0();
     const int i0 = a.slot_off[slot], i1 = a.slot_off[slot + 1];
     for (int k = i0; k < i1; ++k) {
         const int item = a.slot_items[k];
@@ -599,7 +604,7 @@ __global__ __launch_bounds__(512) void chunk_attn_pp_kernel(ChunkAttnArgs a, Dec
         const const_i32* bt_s = (const const_i32*)(a.bt + a.qt_bt[qt]);
         const int j0 = wave * PW;
         const int n_tiles = (ke - kb + 63) / 64;
-        const int wave_qpos_lo = pos0 + j0;
+        const int wave_qpos_lo = pos0 + j0, wave_qpos_hi = pos0 + j0 + PW - 1;
         const bool wave_live = j0 < nrows;
         const bool whole = a.qt_off[qt + 1] - a.qt_off[qt] == 1;
 
@@ -681,10 +686,11 @@ __global__ __launch_bounds__(512) void chunk_attn_pp_kernel(ChunkAttnArgs a, Dec
             bf16x8(&f)[FR] = fr[s % 3];
             if (s < VG) {
                 const int j = s / (NT / 4), n0 = (s % (NT / 4)) * 4, v_base = (2 * j + (grp >> 1)) * PAGE;
+                const int buf = kb + 64 * t > wave_qpos_hi ? 4 : t & 3;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int d = (n0 + i) * 16 + col;
-                    f[i] = *reinterpret_cast<const bf16x8*>(&Vs[t & 3][v_base + d * 16 + vswz(d, grp & 1) * 8]);
+                    f[i] = *reinterpret_cast<const bf16x8*>(&Vs[buf][v_base + d * 16 + vswz(d, grp & 1) * 8]);
                 }
             } else {
                 const int p = s - VG, key = pair_key(col, p & 1), tok = key & 15;
