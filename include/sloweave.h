@@ -402,8 +402,7 @@ int slw_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t out[6]);
  *   chunk attention: query tiles, work items, work-groups per kv head,
  *     1 when every work-group takes whole query tiles (nothing to merge),
  *     largest and smallest number of 64-key tiles a work-group takes, 64-key
- *     tiles in all;
- *   out[11] = 0.
+ *     tiles in all, 1 when the kernel for long work items runs.
  * The same invariants the executor checks on every iteration are checked
  * here (every item list tiles its keys exactly, caps respected).
  * SLW_EINVAL for a bad cfg, negative sizes, prompts beyond max_pos or more

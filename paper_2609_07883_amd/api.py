@@ -333,7 +333,7 @@ def gemm_plan(m: int, n: int, k: int) -> dict:
 
 ATTENTION_PLAN_FIELDS = ("decode_items", "decode_slots", "decode_max_keys", "decode_min_keys",
                          "query_tiles", "chunk_items", "chunk_slots", "chunk_whole",
-                         "chunk_max_tiles", "chunk_min_tiles", "chunk_tiles")
+                         "chunk_max_tiles", "chunk_min_tiles", "chunk_tiles", "chunk_two_phase")
 
 
 def attention_plan(shape, context_lens, prefills=()) -> dict:

@@ -544,9 +544,9 @@ __global__ __launch_bounds__(512) void chunk_attn_kernel(ChunkAttnArgs a, Decode
 //
 // 4096 rows at a 28 K prefix, 8B layer, alone: 1670 -> 1589 us (1.23 -> 1.30
 // PFLOP/s; 1.42 with the softmax left out, about what the power limit leaves
-// the projections too); 2048 rows at 8 K: 278 -> 264 us.  Short chunks lose by
-// the extra slots per item (700 rows at 1000: 30 -> 34 us) and stay with
-// chunk_attn_kernel.
+// the projections too); 2048 rows at 8 K: 278 -> 264 us.  Work items of few
+// tiles lose by the extra slots (700 rows at 1000: 30 -> 34 us) and stay with
+// chunk_attn_kernel, as does head dim 64.
 // ---------------------------------------------------------------------------
 template <int HD, int GROUP, bool DECODE>
 __global__ __launch_bounds__(512) void chunk_attn_pp_kernel(ChunkAttnArgs a, DecodeAttnArgs da) {
@@ -1155,15 +1155,25 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_kernel(ChunkAttnArgs ca
 
 template <int HD, int GROUP>
 void launch_chunk_g(const ChunkAttnArgs& a, hipStream_t s) {
-    if (a.pp) chunk_attn_pp_kernel<HD, GROUP, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
-    else chunk_attn_kernel<HD, GROUP, kChunkStages, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
+    if constexpr (HD == 128) {  // pp is never set at head dim 64
+        if (a.pp) {
+            chunk_attn_pp_kernel<HD, GROUP, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
+            return;
+        }
+    }
+    chunk_attn_kernel<HD, GROUP, kChunkStages, false><<<a.n_slots * a.hkv, 512, 0, s>>>(a, DecodeAttnArgs{});
 }
 
 template <int HD, int GROUP>
 void launch_both_g(const ChunkAttnArgs& ca, const DecodeAttnArgs& da, hipStream_t s) {
     const int blocks = ca.n_slots * ca.hkv + (da.n_slots * da.hkv + 7) / 8;
-    if (ca.pp) chunk_attn_pp_kernel<HD, GROUP, true><<<blocks, 512, 0, s>>>(ca, da);
-    else chunk_attn_kernel<HD, GROUP, kChunkStages, true><<<blocks, 512, 0, s>>>(ca, da);
+    if constexpr (HD == 128) {
+        if (ca.pp) {
+            chunk_attn_pp_kernel<HD, GROUP, true><<<blocks, 512, 0, s>>>(ca, da);
+            return;
+        }
+    }
+    chunk_attn_kernel<HD, GROUP, kChunkStages, true><<<blocks, 512, 0, s>>>(ca, da);
 }
 
 template <int HD, int GROUP>

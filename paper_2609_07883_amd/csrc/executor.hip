@@ -42,12 +42,20 @@ constexpr int kChunkMinTiles = 4;
 // Whole query tiles per work-group when the largest group's load is within
 // 11/10 of an equal share.
 constexpr int64_t kChunkWholeSlackNum = 11, kChunkWholeSlackDen = 10;
-// Work-groups that take whole query tiles, or at least this many 64-key tiles
-// each, run the two-phase chunk kernel: below, its extra phases per work item
-// cost more than the overlap gains (8B layer, old / two-phase us: 37 tiles 80
-// / 79, 34 tiles 83 / 82, 29 tiles 66 / 67, 21 tiles 54 / 55; whole tiles 17
-// tiles 58 / 55, 49 tiles 113 / 107, 900 tiles 1670 / 1589).
-constexpr int64_t kTwoPhaseMinTiles = 32;
+// Work items of at least kTwoPhaseTiles + kTwoPhaseTilesPer64 (positions of a
+// query tile, at least 64, / 64) 64-key tiles on average run the two-phase
+// chunk kernel at head dim 128.  Its fill and extra phases are paid per item,
+// and every wave computes all tiles of the item, which wastes a few more where
+// a query tile holds many positions (few heads a group).  Below the line it
+// loses; at head dim 64 it nearly always did (half the products under the same
+// softmax).  One-phase / two-phase us at n tiles per item:
+//   8B layer (4 heads a group): 1: 11.2 / 13.3, 2 (77 rows at 50): 18.6 / 23.5,
+//   3.5: 28.6 / 34.1, 9.5: 33.1 / 34.9, 17.5: 48.1 / 47.8, 20.2: 63.9 / 64.7,
+//   25.5: 61.8 / 62.6, 27.2: 81.4 / 79.6, 33.5: 76.8 / 75.8, 73: 292 / 272;
+//   2 heads: 28: 77.4 / 80.2, 35: 77.7 / 76.7, 50: 107 / 101;
+//   1 head: 31: 73.6 / 77.0, 36: 81.3 / 85.4, 51: 109.5 / 109.4, 84: 310 / 293;
+//   head dim 64: 1 head, 59: 102 / 108; 8 heads, 72: 108 / 110; 16 heads, 464: 1130 / 1152.
+constexpr int64_t kTwoPhaseTiles = 21, kTwoPhaseTilesPer64 = 5;
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -80,8 +88,8 @@ struct ChunkPlan {
     std::vector<int32_t> slot_off;    // [slots + 1] first entry of each work-group in slot_items
     std::vector<int32_t> slot_items;  // [n] the items of each work-group in turn
     std::vector<int32_t> qt_off;      // [n_qt + 1] first item of each query tile
-    int64_t tiles = 0;                // 64-key tiles of all query tiles
     bool whole = false;               // whole query tiles per work-group
+    bool two_phase = false;           // the two-phase kernel
 };
 
 struct slw_ctx {
@@ -474,7 +482,6 @@ int plan_chunk(const slw_model_cfg& c, int C, const std::vector<int32_t>& qt_pos
     std::vector<int64_t> tile_end(n_qt + 1, 0);
     for (int q = 0; q < n_qt; ++q) tile_end[q + 1] = tile_end[q] + ceil_div(key_end(q), 64);
     const int64_t total_tiles = tile_end[n_qt];
-    p.tiles = total_tiles;
     std::vector<int32_t>& it = p.items;
     int n_slots = 0;
     if (n_qt > 0) {
@@ -534,6 +541,9 @@ int plan_chunk(const slw_model_cfg& c, int C, const std::vector<int32_t>& qt_pos
         p.slot_off.assign(1, 0);
     }
     const int n_items = static_cast<int>(it.size() / 3);
+    const int64_t blocks64 = std::max(1, chunk_tile_positions(c.n_q_heads / c.n_kv_heads) / 64);
+    p.two_phase = c.head_dim == 128 && n_items > 0 &&
+                  total_tiles >= (kTwoPhaseTiles + kTwoPhaseTilesPer64 * blocks64) * n_items;
     p.qt_off.assign(n_qt + 1, 0);
     for (int q = 0, i = 0; q <= n_qt; ++q) {
         while (i < n_items && it[3 * i] < q) ++i;
@@ -752,7 +762,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
             ca.n_items = n_items;
             ca.n_slots = n_slots;
             ca.split = n_items > n_qt ? 1 : 0;
-            ca.pp = cp.whole || cp.tiles >= kTwoPhaseMinTiles * n_slots ? 1 : 0;
+            ca.pp = cp.two_phase ? 1 : 0;
         }
         DecodeAttnArgs da{};
         if (B > 0) {
@@ -894,7 +904,7 @@ extern "C" int slw_attention_plan(const slw_model_cfg* cfg, int32_t B, const int
         }
         const int64_t v[12] = {static_cast<int64_t>(dp.b.size()), dslots, dmax, dmin,
                                static_cast<int64_t>(rows.size()), static_cast<int64_t>(cp.items.size() / 3), cslots,
-                               cp.whole ? 1 : 0, cmax, cmin, ctot, 0};
+                               cp.whole ? 1 : 0, cmax, cmin, ctot, cp.two_phase ? 1 : 0};
         for (int i = 0; i < 12; ++i) out[i] = v[i];
         return SLW_OK;
     });

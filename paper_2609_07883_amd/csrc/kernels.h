@@ -84,7 +84,7 @@ struct ChunkAttnArgs {
     float* part_ml;           // [n_items][hkv][256][2]
     int c, hq, hkv, hd, ld_qkv;
     int n_qt, n_items, n_slots;
-    int pp;                   // the two-phase kernel (long chunks)
+    int pp;                   // the two-phase kernel (long work items, hd 128)
     int split;                // some query tile has several items: the merge kernel runs
 };
 // Query positions per work-group for a group size (rows / group).

@@ -1,7 +1,7 @@
-"""GPU parity of the two-phase chunk kernel, the one long chunks run, for every
-GQA group size and both head dims: a few query rows over a long cached prefix,
-so that each work-group takes at least 32 key tiles, beside decodes in the same
-launch.  Prefix and chunk end inside a page and inside a 64-key tile, the last
+"""GPU parity of the two-phase chunk kernel, the one long work items run at head
+dim 128, for every GQA group size, and of the other chunk kernel over the same
+lengths at head dim 64: a few query rows over a long cached prefix, so that
+each work item takes many key tiles, beside decodes in the same launch.  Prefix and chunk end inside a page and inside a 64-key tile, the last
 query tile is ragged, a run of keys crosses query tiles, and every KV slot that
 no token owns holds NaN (values past the range end are cleared in LDS).
 
@@ -21,9 +21,11 @@ torch = pytest.importorskip("torch")
 # (q heads, kv heads, head dim, chunk, prefix)
 CASES = [
     (16, 16, 64, 300, 16390),
-    (16, 16, 128, 257, 16500),
-    (32, 16, 128, 140, 16500),
+    (16, 16, 128, 257, 32010),
+    (32, 16, 128, 140, 20020),
     (32, 8, 128, 200, 16390),
+    (64, 8, 128, 100, 16401),
+    (128, 8, 128, 50, 16383),
     (64, 8, 64, 100, 16401),
     (128, 8, 64, 50, 16383),
 ]
@@ -39,7 +41,7 @@ def test_long_prefix(case):
                        rms_eps=1e-5, rope_theta=10000.0, max_pos=32768)
     dec, ctx = [21, 22], [5, 700]
     plan = api.attention_plan(shape, ctx, [(P, C)])
-    assert plan["chunk_whole"] or plan["chunk_tiles"] >= 32 * plan["chunk_slots"]
+    assert plan["chunk_two_phase"] == (hd == 128)
     qk_std = 0.16 * (64 / hd) ** 0.25
     sess = Session(shape, num_blocks=(P + C) // 16 + 60, max_c=C, max_b=2, qk_std=qk_std)
     sess.k_pool.fill_(float("nan"))
@@ -87,6 +89,7 @@ def test_non_finite_row_reaches_no_earlier_key_tile(case, bad):
     first_bad = (P + r) // 64 * 64 - P               # first chunk row whose key tile holds row r
     safe = r // tile * tile + max(0, first_bad - r // tile * tile) // pw * pw
     assert safe > r // tile * tile                   # rows of r's own query tile among them
+    assert api.attention_plan(shape, ctx, [(P, C)])["chunk_two_phase"]
     sess = Session(shape, num_blocks=(P + C) // 16 + 60, max_c=C, max_b=2, qk_std=0.16 * (64 / hd) ** 0.25)
     gen = torch.Generator(device=sess.dev).manual_seed(3)
     sess.k_pool.normal_(0.0, 1.0, generator=gen)

@@ -365,6 +365,20 @@ def test_attention_plans_cover_every_key_once_and_balance(ctx, pre, shape):
             assert p["chunk_max_tiles"] <= share
 
 
+def test_only_long_work_items_take_the_two_phase_chunk_kernel():
+    """The two-phase chunk kernel pays its extra phases per work item: items of
+    a few 64-key tiles stay with the other kernel, also where a work-group
+    takes whole query tiles, and head dim 64 always does."""
+    sh = synth.LLAMA8B_LAYER
+    for pre in ([(0, 1)], [(0, 64)], [(50, 77)], [(128, 128)], [(0, 256)], [(0, 64)] * 8, [(0, 256)] * 16,
+                [(700, 128)] * 16, [(0, 1024)], [(0, 2048)], [(2048, 512)], [(28672, 64)]):
+        assert api.attention_plan(sh, [100] * 8, pre)["chunk_two_phase"] == 0, pre
+        assert api.attention_plan(synth.TINY, [100], [(p % 1024, c) for p, c in pre])["chunk_two_phase"] == 0
+    for pre in ([(8192, 2048)], [(28672, 4096)], [(0, 4096)], [(4000, 128)] * 16):
+        assert api.attention_plan(sh, [100] * 8, pre)["chunk_two_phase"] == 1, pre
+    assert api.attention_plan(sh, [100], [])["chunk_two_phase"] == 0
+
+
 def test_attention_plan_examples():
     """Long prompts take whole query tiles (nothing to merge); the start of a
     prompt, whose tiles grow with their position, is cut into runs; one
