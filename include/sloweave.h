@@ -210,9 +210,11 @@ int slw_mixed_iteration(slw_ctx* ctx, const slw_batch* batch, const void* x_in, 
  * copied from host memory the context already holds, `stream` is
  * synchronised once after that copy (the iteration's kernels then run
  * asynchronously), both attentions run on `stream`, and no stage timing is
- * recorded.  An iteration whose workspace would exceed the array
- * (slw_workspace_size(ctx, C, B) gives an upper bound) is refused with
- * SLW_ENOMEM before anything is reserved or enqueued.  Every call on a GPU
+ * recorded.  Where only the partial sums of split products do not fit the
+ * array, those products run in blocks of rows, with the same results; an
+ * iteration whose other buffers exceed the array is refused with SLW_ENOMEM
+ * before anything is reserved or enqueued (slw_workspace_size(ctx, C, B) at
+ * most SLW_STATIC_WS_BYTES is enough to be accepted).  Every call on a GPU
  * shares that GPU's array, which keeps the last call's contents: calls that
  * overlap on one GPU (several streams or threads) race.
  */

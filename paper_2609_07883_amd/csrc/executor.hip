@@ -166,6 +166,7 @@ size_t meta_ints(const slw_model_cfg& c, int C, int B) {
 
 struct Layout {
     size_t xn, qkv, attn, h, act, rope, meta, part_o, part_ml, cpart_o, cpart_ml, gemm_part, end_fixed;
+    size_t gemm_part_bytes;  // from gemm_part on; set where the workspace is known
 };
 
 Layout layout(const slw_model_cfg& c, int C, int B) {
@@ -203,11 +204,9 @@ struct LayerPlans {
     }
 };
 
-LayerPlans plan_layer(const slw_model_cfg& c, int M, int max_splits = kMaxSplits) {
-    return {plan_gemm(M, qkv_width(c), c.d_model, false, max_splits),
-            plan_gemm(M, c.d_model, c.n_q_heads * c.head_dim, false, max_splits),
-            plan_gemm(M, 2 * c.ffn_dim, c.d_model, true, max_splits),
-            plan_gemm(M, c.d_model, c.ffn_dim, false, max_splits)};
+LayerPlans plan_layer(const slw_model_cfg& c, int M) {
+    return {plan_gemm(M, qkv_width(c), c.d_model, false), plan_gemm(M, c.d_model, c.n_q_heads * c.head_dim, false),
+            plan_gemm(M, 2 * c.ffn_dim, c.d_model, true), plan_gemm(M, c.d_model, c.ffn_dim, false)};
 }
 
 int check_cfg(const slw_model_cfg& c) {
@@ -352,16 +351,21 @@ int mixed_iteration_impl(slw_ctx* ctx, const slw_batch* bt, const void* x_in, vo
             req.emplace_back(id, L + 1);
         }
     }
-    const Layout L = layout(c, C, B);
-    LayerPlans plans = plan_layer(c, C + B);
-    // the static array also takes an iteration whose split-K partials alone
-    // would not fit, with the products unsplit
-    if (no_alloc && ws_bytes < L.end_fixed + plans.partial_bytes()) plans = plan_layer(c, C + B, 1);
-    const size_t gpart = plans.partial_bytes();
-    if (ws_bytes < L.end_fixed + gpart)
+    Layout L = layout(c, C, B);
+    const LayerPlans plans = plan_layer(c, C + B);
+    size_t need = L.end_fixed + plans.partial_bytes();
+    // The static array also takes an iteration whose split-K partials alone
+    // would not fit: they then share the room of the attention partials, which
+    // no product runs beside, and the products run in blocks of as many rows
+    // as fit there, with the same plans and so the same results.
+    if (no_alloc && ws_bytes < need) {
+        L.gemm_part = L.part_o;
+        need = std::max(L.end_fixed, L.gemm_part + plans.partial_bytes() / (C + B));
+    }
+    if (ws_bytes < need)
         return fail(SLW_ENOMEM, "%s holds %zu bytes, this iteration needs %zu",
-                    no_alloc ? "the static workspace (SLW_STATIC_WS_BYTES)" : "the workspace", ws_bytes,
-                    L.end_fixed + gpart);
+                    no_alloc ? "the static workspace (SLW_STATIC_WS_BYTES)" : "the workspace", ws_bytes, need);
+    L.gemm_part_bytes = ws_bytes - L.gemm_part;
     int rc = SLW_OK;
     if (!no_alloc) {
         rc = ensure_hip(ctx);
@@ -730,7 +734,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
             ga.hq = hq;
             ga.hkv = hkv;
             ga.hd = hd;
-            launch_gemm(ga, plans.qkv, gpartp, stream);
+            launch_gemm(ga, plans.qkv, gpartp, L.gemm_part_bytes, stream);
         }
         if ((rc = mark(l, 3))) return rc;
         // Both attentions in one launch; per-stage events separate them.
@@ -799,7 +803,7 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         launch_attention_merge(&ca, &da, stream);
         if ((rc = mark(l, 6))) return rc;
         launch_gemm(GemmArgs{attn, wl.wo, hbuf, cur, M, d, hq * hd, hq * hd, d, EPI_RESID_F32OUT}, plans.o, gpartp,
-                    stream);
+                    L.gemm_part_bytes, stream);
         if ((rc = mark(l, 7))) return rc;
         const bool gu_norm = plans.gu.cfg == kStreamCfg;  // that kernel normalises its rows itself
         if (!gu_norm) launch_rmsnorm(hbuf, true, wl.g2, xn, M, d, c.rms_eps, stream);
@@ -810,10 +814,11 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
                 ga.norm_g = wl.g2;
                 ga.norm_eps = c.rms_eps;
             }
-            launch_gemm(ga, plans.gu, gpartp, stream);
+            launch_gemm(ga, plans.gu, gpartp, L.gemm_part_bytes, stream);
         }
         if ((rc = mark(l, 9))) return rc;
-        launch_gemm(GemmArgs{act, wl.wd, x_out, hbuf, M, d, F, F, d, EPI_RESID_F32IN}, plans.d, gpartp, stream);
+        launch_gemm(GemmArgs{act, wl.wd, x_out, hbuf, M, d, F, F, d, EPI_RESID_F32IN}, plans.d, gpartp,
+                    L.gemm_part_bytes, stream);
         if ((rc = mark(l, 10))) return rc;
     }
     HIP_TRY(hipGetLastError());

@@ -826,6 +826,7 @@ constexpr TileCfg kCfgs[] = {{256, 256, 1, 1.253f}, {224, 256, 1, 1.108f}, {192,
                              {96, 128, 2, 0.435f},  {64, 128, 2, 0.396f}};
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr int kCus = 256;
+constexpr int kMaxSplits = 8;
 
 template <class T, int EPI>
 void launch_tile(const GemmArgs& g, const GemmPlan& p, float* part, hipStream_t s) {
@@ -924,7 +925,7 @@ float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
 // counts, where each of its work-groups re-reads all activation rows, take the tile kernel with the configuration and split that
 // predict_us ranks first.  n must be a multiple of 128 and k of 64; a split
 // keeps at least 512 of k.
-GemmPlan plan_gemm(int m, int n, int k, bool swiglu, int max_splits) {
+GemmPlan plan_gemm(int m, int n, int k, bool swiglu) {
     const bool wide = n >= 16384, qkv_like = n >= 6144 && !wide;
     if (swiglu && wide && m <= kStreamMaxRows && stream_k_ok(k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
     if (!wide && (m <= 8 || (m <= 24 && !qkv_like && k < 8192))) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
@@ -933,7 +934,7 @@ GemmPlan plan_gemm(int m, int n, int k, bool swiglu, int max_splits) {
     float best = 0.f;
     for (int c = 0; c < kNumCfgs; ++c) {
         if (n % kCfgs[c].bn) continue;
-        for (int sp = 1; sp <= max_splits && (sp == 1 || (k % (64 * sp) == 0 && k / sp >= 512)); sp *= 2) {
+        for (int sp = 1; sp <= kMaxSplits && (sp == 1 || (k % (64 * sp) == 0 && k / sp >= 512)); sp *= 2) {
             const float t = predict_us(kCfgs[c], sp, m32, n, k);
             if (best == 0.f || t < best) {
                 best = t;
@@ -977,8 +978,30 @@ bool gemm_shape_ok(const GemmPlan& p, int n, int k) {
     return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 
-void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t s) {
+void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, size_t partial_bytes, hipStream_t s) {
     if (g.m <= 0) return;
+    const size_t row_bytes = static_cast<size_t>(p.splits) * g.n * sizeof(float);
+    if (p.splits > 1 && g.m * row_bytes > partial_bytes) {
+        // whole tile rows to a block where one fits; no result depends on the
+        // rows beside it
+        int rows = static_cast<int>(partial_bytes / row_bytes);
+        if (rows > p.bm) rows -= rows % p.bm;
+        const bool out_f32 = g.epi == EPI_RESID_F32OUT, resid_f32 = g.epi == EPI_RESID_F32IN;
+        for (int r = 0; r < g.m; r += rows) {
+            GemmArgs b = g;
+            const size_t o = static_cast<size_t>(r) * g.ldo;
+            b.m = std::min(rows, g.m - r);
+            b.a = static_cast<const char*>(g.a) + static_cast<size_t>(r) * g.lda * 2;
+            b.out = static_cast<char*>(g.out) + o * (out_f32 ? 4 : 2);
+            if (g.resid) b.resid = static_cast<const char*>(g.resid) + o * (resid_f32 ? 4 : 2);
+            if (g.epi == EPI_QKV) {
+                b.rope_cs = g.rope_cs + static_cast<size_t>(r) * (g.hd / 2);
+                b.slot = g.slot + r;
+            }
+            launch_gemm(b, p, partial, partial_bytes, s);
+        }
+        return;
+    }
     if (p.cfg == kNarrowCfg) {  // plans cover m <= 32
         if (g.m <= 16) launch_narrow<1>(g, p, s);
         else launch_narrow<2>(g, p, s);

@@ -48,15 +48,16 @@ struct GemmPlan {
 };
 constexpr int kStreamCfg = 99;  // the weight-streaming kernel (gate/up, m <= 8), which takes unnormalised rows
 constexpr int kNarrowCfg = 98;  // the narrow kernel (m <= 32, k split inside the work-group)
-constexpr int kMaxSplits = 8;
 // swiglu: the gate/up projection
-GemmPlan plan_gemm(int m, int n, int k, bool swiglu, int max_splits = kMaxSplits);
+GemmPlan plan_gemm(int m, int n, int k, bool swiglu);
 // The plan for a given configuration and k split.
 GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k);
 // Whether the plan's tiles divide n and its splits k.
 bool gemm_shape_ok(const GemmPlan& p, int n, int k);
-// Enqueue the GEMM; `partial` must hold plan.partial_bytes when plan.splits > 1.
-void launch_gemm(const GemmArgs& g, const GemmPlan& plan, void* partial, hipStream_t s);
+// Enqueue the GEMM.  A plan with splits > 1 writes partial sums to `partial`,
+// `partial_bytes` of them: fewer than plan.partial_bytes (but those of one row
+// at least) make it run in blocks of rows one after the other, with the same results.
+void launch_gemm(const GemmArgs& g, const GemmPlan& plan, void* partial, size_t partial_bytes, hipStream_t s);
 
 // Causal chunk-vs-prefix attention over the prefill sequences' pages.
 // A query tile holds up to 256 / group consecutive chunk rows of one prefill
