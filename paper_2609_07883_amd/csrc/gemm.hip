@@ -608,13 +608,17 @@ __device__ __forceinline__ int w_row(const GemmArgs& g, int c) {
 // kernel of 448 work-groups: 50.1 -> 46 us at 1 row (235 MB: 5.1 TB/s), 52.9 ->
 // 50 at 8; at 16 rows 58 against 49 for RMSNorm and the tile kernel.  The same
 // for the qkv projection lost at every row count (19.5 against 18.9 us at 1 row,
-// 24 against 21 at 8): two units a CU do not pay for the rows' read.
+// 24 against 21 at 8): two units a CU do not pay for the rows' read.  Rows past
+// 6144 do not fit the registers in fp32 and are read twice.
 // ---------------------------------------------------------------------------
 constexpr int kStreamMaxRows = 8;
 // slices in flight per wave, a divisor of the slices of a unit
-constexpr int stream_ring(int ns) { return ns % 8 == 0 ? 8 : ns % 10 == 0 ? 10 : 6; }
-// k = 256 NS; beyond 6144 the rows no longer fit the registers
-constexpr bool stream_k_ok(int k) { return k % 1024 == 0 && k >= 2048 && k <= 6144; }
+constexpr int stream_ring(int ns) {
+    for (int r : {8, 10, 9, 7, 11, 13, 6})
+        if (ns % r == 0) return r;
+    return ns;
+}
+// k = 256 NS, NS even, from 4 to 32.
 
 template <int NS>
 __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, int per_wg) {
@@ -640,20 +644,32 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
     // stored), read once and normalised in registers
     bf16x8 af[NS];
     {
-        const size_t arow = static_cast<size_t>(min(j, g.m - 1)) * g.lda + kbeg;
-        f32x4 raw[NS][2];
+        // rows of up to 6144 stay in registers between the sum of squares and
+        // the scaling; longer ones are read twice
+        constexpr bool KEEP = NS <= 24;
+        const float* src = static_cast<const float*>(g.a) + static_cast<size_t>(min(j, g.m - 1)) * g.lda + kbeg;
+        auto half = [&](int s, int h) { return *reinterpret_cast<const f32x4*>(src + 32 * s + 4 * h); };
+        f32x4 raw[KEEP ? NS : 1][2];
         float ss = 0.f;
+        if constexpr (KEEP) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(static_cast<const float*>(g.a) + arow + 32 * s);
-            raw[s][0] = src[0];
-            raw[s][1] = src[1];
+            for (int s = 0; s < NS; ++s) {
+                raw[s][0] = half(s, 0);
+                raw[s][1] = half(s, 1);
+            }
         }
-        auto x = [&](int s, int e) { return raw[s][e / 4][e % 4]; };
+        auto x = [&](int s, int h) {
+            if constexpr (KEEP) return raw[s][h];
+            else return half(s, h);
+        };
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) ss += x(s, e) * x(s, e);
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 v = x(s, h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ss += v[e] * v[e];
+            }
         ss += __shfl_xor(ss, 16, 64);
         ss += __shfl_xor(ss, 32, 64);
         if (grp == 0) ssq[ks][j] = ss;
@@ -667,7 +683,11 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
         for (int s = 0; s < NS; ++s) {
             const bf16x8 gain = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(g.norm_g) + kbeg + 32 * s);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) af[s][e] = f2bf(x(s, e) * inv * bf2f(gain[e]));
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 v = x(s, h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) af[s][4 * h + e] = f2bf(v[e] * inv * bf2f(gain[4 * h + e]));
+            }
         }
     }
 
@@ -858,12 +878,22 @@ void launch_stream_ns(const GemmArgs& g, hipStream_t s) {
 }
 
 void launch_stream(const GemmArgs& g, hipStream_t s) {
-    switch (g.k / 1024) {  // stream_k_ok
-        case 2: launch_stream_ns<8>(g, s); break;
-        case 3: launch_stream_ns<12>(g, s); break;
-        case 4: launch_stream_ns<16>(g, s); break;
-        case 5: launch_stream_ns<20>(g, s); break;
-        default: launch_stream_ns<24>(g, s); break;
+    switch (g.k / 512) {  // stream_shape_ok
+        case 2: launch_stream_ns<4>(g, s); break;
+        case 3: launch_stream_ns<6>(g, s); break;
+        case 4: launch_stream_ns<8>(g, s); break;
+        case 5: launch_stream_ns<10>(g, s); break;
+        case 6: launch_stream_ns<12>(g, s); break;
+        case 7: launch_stream_ns<14>(g, s); break;
+        case 8: launch_stream_ns<16>(g, s); break;
+        case 9: launch_stream_ns<18>(g, s); break;
+        case 10: launch_stream_ns<20>(g, s); break;
+        case 11: launch_stream_ns<22>(g, s); break;
+        case 12: launch_stream_ns<24>(g, s); break;
+        case 13: launch_stream_ns<26>(g, s); break;
+        case 14: launch_stream_ns<28>(g, s); break;
+        case 15: launch_stream_ns<30>(g, s); break;
+        default: launch_stream_ns<32>(g, s); break;
     }
 }
 
@@ -913,10 +943,25 @@ float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
     return t;
 }
 
+// Whether a gate/up projection of few rows streams its weights (k of a size
+// the kernel is built for).  Multiples of 1024 from 2048 to 6144 do at any width.
+// The others do where the tile kernel stands badly: for k below 2048, and at
+// widths whose 128-column tiles leave its second round of work-groups less than half
+// full.  Norm and gate/up stages, tile kernel / streamed, us at 1 and 8 rows:
+// k 3584, n 37888: 71 / 62, 71 / 67; k 6656, n 37888: 125 / 102, 126 / 111;
+// k 7168, n 40960: 134 / 121, 134 / 130; k 1024, n 16384: 20 / 17, 20 / 17;
+// and outside, where it can lose: k 7168, n 28672: 79 / 91, 79 / 99.
+bool stream_shape_ok(int n, int k) {
+    if (k % 512 || k < 1024 || k > 8192) return false;
+    if (k % 1024 == 0 && k >= 2048 && k <= 6144) return true;
+    const int tiles = n / 128;
+    return 2 * tiles < 3 * kCus && (k < 2048 || tiles > kCus);
+}
+
 }  // namespace
 
 // Wide gate/up projections of up to 8 rows take the weight-streaming kernel with
-// the norm folded in, where k is one it is built for.
+// the norm folded in, where their shape suits it.
 // The narrow kernel takes qkv- and down-like projections up to 8 rows and the
 // output projection up to 24 (8B layer, against the tile kernel, us at 1 / 8 /
 // 24 rows: output 8.4 / 9.2 / 12.4 against 11.6 / 12.1 / 12.4; down 21.6 /
@@ -927,7 +972,7 @@ float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
 // keeps at least 512 of k.
 GemmPlan plan_gemm(int m, int n, int k, bool swiglu) {
     const bool wide = n >= 16384, qkv_like = n >= 6144 && !wide;
-    if (swiglu && wide && m <= kStreamMaxRows && stream_k_ok(k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
+    if (swiglu && wide && m <= kStreamMaxRows && stream_shape_ok(n, k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
     if (!wide && (m <= 8 || (m <= 24 && !qkv_like && k < 8192))) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
     int cfg = kNumCfgs - 1, splits = 1;
     const int m32 = (m + 31) / 32 * 32;
@@ -974,7 +1019,7 @@ GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k) {
 bool gemm_shape_ok(const GemmPlan& p, int n, int k) {
     if (p.cfg == kNarrowCfg)  // m <= 32 is the caller's part; paired epilogues need 64-column tiles
         return n % 64 == 0 && p.ks >= 1 && p.ks <= 8 && k % (32 * p.ks) == 0;
-    if (p.cfg == kStreamCfg) return n % 16 == 0 && stream_k_ok(k);  // m <= 8 and the SwiGLU epilogue are the caller's part
+    if (p.cfg == kStreamCfg) return n % 16 == 0 && stream_shape_ok(n, k);  // m <= 8 and the SwiGLU epilogue are the caller's part
     return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 

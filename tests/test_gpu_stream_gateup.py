@@ -2,13 +2,16 @@
 row counts at both ends of its range, hidden sizes that take different register
 rings (8, 6 and 10 slices), and an FFN width whose 1032 units of eight outputs
 do not divide evenly over the work-groups.  Every stage of decode-only
-iterations against the float64 oracle at the parity bar.
+iterations against the float64 oracle at the parity bar.  Then every hidden
+size the kernel is built for, its outputs against a float64 product of the
+residual rows the same iteration left.
 """
+import numpy as np
 import pytest
 
 from paper_2609_07883_amd import api, synth
 from paper_2609_07883_amd.synth import ModelShape
-from tests.parity import TOL, Mirror, check, stage_errors
+from tests.parity import RMS_TOL, TOL, Mirror, check, rel_err, rms_err, stage_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -38,3 +41,37 @@ def test_few_rows(d_model):
         for name, e in stage_errors(mir, b, x).items():
             assert e["rel"] <= TOL, (rows, name, e)
         check(y, yr, f"d_model {d_model}, {rows} rows")
+
+
+# multiples of 1024 from 2048 to 6144 stream at any width from 16384 on; the
+# others where 128-column tiles are 257 to 383 (n = 2 ffn), below 2048 also fewer
+SIZES = [(1024, 8256), (1536, 8256), (2048, 8256), (2560, 16448), (3072, 8256), (3584, 18944), (4096, 8256),
+         (4608, 16448), (5120, 8256), (5632, 16448), (6144, 8256), (6656, 17920), (7168, 16448), (7680, 16448),
+         (8192, 16448)]
+
+
+@pytest.mark.parametrize("d_model,ffn", SIZES)
+def test_every_hidden_size(d_model, ffn):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_07883_amd.runtime import Session, tensor_to_f64
+    shape = ModelShape(n_layers=1, d_model=d_model, n_q_heads=4, n_kv_heads=1, head_dim=128, ffn_dim=ffn,
+                       rms_eps=1e-5, rope_theta=10000.0, max_pos=1024)
+    assert api.gemm_plan(8, 2 * ffn, d_model)["cfg"] == api.GEMM_SKINNY
+    assert api.gemm_plan(9, 2 * ffn, d_model)["cfg"] != api.GEMM_SKINNY
+    sess = Session(shape, num_blocks=16, max_c=0, max_b=8, device_weights=True)
+    for sid in range(8):
+        sess.ctx.seq_create(sid)
+    w = sess.weights[0]
+    g2, wgu = w["g2"].double(), w["wgu"].double()
+    for rows in (1, 3, 8):
+        b = api.Batch(0, 0, 0, list(range(rows)), [0] * rows)
+        x = synth.embeddings(rows, d_model, seed=1, stream=rows)
+        sess.run(b, x)
+        h = torch.from_numpy(sess.view(api.VIEW_H, 0, rows, d_model, fp32=True)).to(sess.dev)
+        act = sess.view(api.VIEW_ACT, 0, rows, ffn)
+        n = h / torch.sqrt((h * h).mean(1, keepdim=True) + shape.rms_eps) * g2
+        gate, up = (n @ wgu.T).split(ffn, 1)
+        ref = tensor_to_f64(gate / (1 + torch.exp(-gate)) * up)
+        assert np.isfinite(act).all()
+        assert rel_err(act, ref) <= TOL and rms_err(act, ref) <= RMS_TOL, (rows, rel_err(act, ref))
