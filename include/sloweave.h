@@ -388,7 +388,7 @@ int slw_fill_normal(void* dst, size_t n, uint64_t seed, float mean, float std, v
  * kernel variant a row count reaches.  out[0..5]: tile configuration (99: the
  * weight-streaming kernel of gate/up, taken to be a projection with n >= 16384,
  * for m <= 8, which also applies the RMSNorm before it; 98: the narrow kernel
- * for m <= 24, k split over the waves of a work-group), tile rows BM, tile
+ * for m <= 24, or 32 where n <= 3072, k split over the waves of a work-group), tile rows BM, tile
  * columns BN, k split factor (1: none), then 0 and 0.
  * m >= 1; n a multiple of 128 and k of 64, else SLW_EINVAL.
  */

@@ -966,14 +966,19 @@ bool stream_shape_ok(int n, int k) {
 // output projection up to 24 (8B layer, against the tile kernel, us at 1 / 8 /
 // 24 rows: output 8.4 / 9.2 / 12.4 against 11.6 / 12.1 / 12.4; down 21.6 /
 // 25.8 at 1 / 8 rows against 25.5 / 26.0, 31.5 against 26.3 at 16; qkv 14.2 /
-// 15.4 against 14.0 / 14.7 and no reduction launch).  Larger row
-// counts, where each of its work-groups re-reads all activation rows, take the tile kernel with the configuration and split that
-// predict_us ranks first.  n must be a multiple of 128 and k of 64; a split
-// keeps at least 512 of k.
+// 15.4 against 14.0 / 14.7 and no reduction launch), and all 32 rows it has
+// where the tile kernel's few work-groups would need a split of k and its
+// reduction (a layer at 25 / 32 rows, tile kernel against narrow: d_model 1024,
+// FFN 4096: 59.6 / 59.4 against 54.6 / 56.4 us; d_model 3072, output only:
+// 96.9 / 97.9 against 95.8 / 97.6).  Larger row counts, where each of its
+// work-groups re-reads all activation rows, take the tile kernel with the
+// configuration and split that predict_us ranks first.  n must be a multiple
+// of 128 and k of 64; a split keeps at least 512 of k.
 GemmPlan plan_gemm(int m, int n, int k, bool swiglu) {
     const bool wide = n >= 16384, qkv_like = n >= 6144 && !wide;
     if (swiglu && wide && m <= kStreamMaxRows && stream_shape_ok(n, k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
-    if (!wide && (m <= 8 || (m <= 24 && !qkv_like && k < 8192))) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
+    const int narrow_rows = qkv_like || k >= 8192 ? 8 : n <= 3072 && k >= 1024 ? 32 : 24;
+    if (!wide && m <= narrow_rows) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
     int cfg = kNumCfgs - 1, splits = 1;
     const int m32 = (m + 31) / 32 * 32;
     float best = 0.f;

@@ -42,3 +42,31 @@ def test_short_k_ranges(ffn, rows):
         assert e["rel"] <= TOL, (name, e)
     check(y, yr, f"ffn {ffn}, {rows} rows")
     assert mir.kv_error(b) <= TOL
+
+
+@pytest.mark.parametrize("rows", [24, 25, 32, 33])
+def test_narrow_widths_at_the_narrow_kernels_last_rows(rows):
+    """Projections of at most 3072 columns stay with the narrow kernel up to 32
+    rows (two 16-row groups, the second one ragged at 25): decode-only
+    iterations on both sides of the limit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_07883_amd.runtime import Session
+    shape = ModelShape(n_layers=1, d_model=1024, n_q_heads=16, n_kv_heads=16, head_dim=64, ffn_dim=1536,
+                       rms_eps=1e-5, rope_theta=10000.0, max_pos=1024)
+    for n, k in ((3072, 1024), (1024, 1024), (1024, 1536)):
+        assert (api.gemm_plan(rows, n, k)["cfg"] == api.GEMM_NARROW) == (rows <= 32)
+    sess = Session(shape, num_blocks=64, max_c=0, max_b=rows, layers=[synth.layer_weights(shape, std=0.03)])
+    mir = Mirror(sess)
+    ids, ctx = list(range(1, rows + 1)), [i % 19 for i in range(rows)]
+    for sid, n in zip(ids, ctx):
+        mir.create(sid)
+        mir.install_context(sid, n)
+    b = api.Batch(0, 0, 0, ids, ctx)
+    x = synth.embeddings(rows, shape.d_model, seed=1, stream=rows)
+    y, yr, sg, sr = mir.step(b, x)
+    assert sg == sr
+    for name, e in stage_errors(mir, b, x).items():
+        assert e["rel"] <= TOL, (name, e)
+    check(y, yr, f"{rows} rows")
+    assert mir.kv_error(b) <= TOL
