@@ -386,10 +386,12 @@ int slw_fill_normal(void* dst, size_t n, uint64_t seed, float mean, float std, v
  * The GEMM plan an iteration uses for a projection out[m][n] = A[m][k] W^T
  * (host only, touches no GPU), for callers and tests that need to know which
  * kernel variant a row count reaches.  out[0..5]: tile configuration (99: the
- * weight-streaming kernel of gate/up, taken to be a projection with n >= 16384,
- * for m <= 8, which also applies the RMSNorm before it; 98: the narrow kernel
- * for m <= 24, or 32 where n <= 3072, k split over the waves of a work-group), tile rows BM, tile
- * columns BN, k split factor (1: none), then 0 and 0.
+ * weight-streaming kernel of gate/up projections with n >= 16384, for m <= 8,
+ * which also applies the RMSNorm before it; 98: the narrow kernel for m <= 24,
+ * or 32 where n <= 3072, k split over the waves of a work-group), tile rows BM,
+ * tile columns BN, k split factor (1: none); then tile configuration and k
+ * split factor of a projection of this size that is not gate/up, which differ
+ * from out[0] and out[3] only where that is 99.
  * m >= 1; n a multiple of 128 and k of 64, else SLW_EINVAL.
  */
 int slw_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t out[6]);

@@ -320,15 +320,17 @@ def fill_normal(dst: int, n: int, seed: int, mean: float, std: float, stream: in
     _check(lib().slw_fill_normal(dst or None, int(n), int(seed), float(mean), float(std), stream or None))
 
 
-GEMM_SKINNY = 99
+GEMM_STREAM = 99
 GEMM_NARROW = 98
+GEMM_SKINNY = GEMM_STREAM   # the name of the kernel before it
 
 
 def gemm_plan(m: int, n: int, k: int) -> dict:
-    """The GEMM plan an iteration uses for out[m][n] = A[m][k] W^T (host only)."""
+    """The GEMM plan an iteration uses for out[m][n] = A[m][k] W^T (host only);
+    other_cfg and other_splits: for a projection of this size that is not gate/up."""
     out = np.zeros(6, np.int32)
     _check(lib().slw_gemm_plan(int(m), int(n), int(k), _ptr(out, C.c_int32)))
-    return dict(zip(("cfg", "bm", "bn", "splits", "sk_workers", "dp_tiles"), (int(v) for v in out)))
+    return dict(zip(("cfg", "bm", "bn", "splits", "other_cfg", "other_splits"), (int(v) for v in out)))
 
 
 ATTENTION_PLAN_FIELDS = ("decode_items", "decode_slots", "decode_max_keys", "decode_min_keys",

@@ -919,8 +919,8 @@ extern "C" int slw_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t out[6]) {
     if (!out) return fail(SLW_EINVAL, "null argument");
     if (m < 1 || n < 128 || n % 128 || k < 64 || k % 64)
         return fail(SLW_EINVAL, "m >= 1, n a multiple of 128 and k of 64 (got %d, %d, %d)", m, n, k);
-    const GemmPlan p = plan_gemm(m, n, k, true);
-    const int32_t v[6] = {p.cfg, p.bm, p.bn, p.splits, 0, 0};
+    const GemmPlan p = plan_gemm(m, n, k, true), q = plan_gemm(m, n, k, false);
+    const int32_t v[6] = {p.cfg, p.bm, p.bn, p.splits, q.cfg, q.splits};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
     return SLW_OK;
 }

@@ -102,7 +102,7 @@ def test_chat_bursty_point():
 
 
 def test_decode_only_batch():
-    """C = 0, B = 64: every GEMM runs the weight-streaming kernel on 64 rows."""
+    """C = 0, B = 64: a decode batch on the tile kernel, k split for three of the projections."""
     ctx = synth.lognormal_lengths(64, 700, 0.8, 8192, seed=2)
     _run(0, 0, ctx, seed=15)
 
@@ -133,7 +133,7 @@ def test_small_decode_batches(B):
 @functools.lru_cache(maxsize=None)
 def _plan_cover():
     """Row counts that together reach every GEMM variant (tile configuration,
-    epilogue, plain / split-K / stream-K) the planner picks for the four
+    epilogue, plain / split-K) the planner picks for the four
     projections of this layer between 33 and 4104 rows, chosen greedily from
     the plans the library reports."""
     shape = synth.LLAMA8B_LAYER
@@ -145,7 +145,7 @@ def _plan_cover():
         out = set()
         for name, (n, k) in proj.items():
             p = api.gemm_plan(m, n, k)
-            mode = "sk" if p["sk_workers"] else "split" if p["splits"] > 1 else "plain"
+            mode = "split" if p["splits"] > 1 else "plain"
             out.add((name, p["cfg"], mode))
         return out
 

@@ -70,3 +70,30 @@ def test_narrow_widths_at_the_narrow_kernels_last_rows(rows):
         assert e["rel"] <= TOL, (name, e)
     check(y, yr, f"{rows} rows")
     assert mir.kv_error(b) <= TOL
+
+
+@pytest.mark.parametrize("rows", [3, 8])
+def test_few_rows_of_a_qkv_projection_as_wide_as_gate_up(rows):
+    """160 heads of 128: 20480 qkv columns at row counts where a gate/up
+    projection of that width streams its weights."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_07883_amd.runtime import Session
+    shape = ModelShape(n_layers=1, d_model=1024, n_q_heads=128, n_kv_heads=16, head_dim=128, ffn_dim=128,
+                       rms_eps=1e-5, rope_theta=10000.0, max_pos=1024)
+    p = api.gemm_plan(rows, 20480, 1024)
+    assert p["cfg"] == api.GEMM_STREAM and p["other_cfg"] != api.GEMM_STREAM
+    sess = Session(shape, num_blocks=16, max_c=0, max_b=rows)
+    mir = Mirror(sess)
+    ids, ctx = list(range(1, rows + 1)), [i % 19 for i in range(rows)]
+    for sid, n in zip(ids, ctx):
+        mir.create(sid)
+        mir.install_context(sid, n)
+    b = api.Batch(0, 0, 0, ids, ctx)
+    x = synth.embeddings(rows, shape.d_model, seed=1, stream=rows)
+    y, yr, sg, sr = mir.step(b, x)
+    assert sg == sr
+    for name, e in stage_errors(mir, b, x).items():
+        assert e["rel"] <= TOL, (name, e)
+    check(y, yr, f"{rows} rows")
+    assert mir.kv_error(b) <= TOL

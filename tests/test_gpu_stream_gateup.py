@@ -32,7 +32,7 @@ def test_few_rows(d_model):
         mir.create(sid)
         mir.install_context(sid, n)
     for step, rows in enumerate([1, 7, 8, 9]):  # 9: RMSNorm and the tile kernel
-        assert (api.gemm_plan(rows, 2 * shape.ffn_dim, d_model)["cfg"] == api.GEMM_SKINNY) == (rows <= 8)
+        assert (api.gemm_plan(rows, 2 * shape.ffn_dim, d_model)["cfg"] == api.GEMM_STREAM) == (rows <= 8)
         lens = [n + sum(1 for r in [1, 7, 8, 9][:step] if i < r) for i, n in enumerate(ctx[:rows])]
         b = api.Batch(0, 0, 0, ids[:rows], lens)
         x = synth.embeddings(rows, d_model, seed=1, stream=rows)
@@ -57,8 +57,8 @@ def test_every_hidden_size(d_model, ffn):
     from paper_2609_07883_amd.runtime import Session, tensor_to_f64
     shape = ModelShape(n_layers=1, d_model=d_model, n_q_heads=4, n_kv_heads=1, head_dim=128, ffn_dim=ffn,
                        rms_eps=1e-5, rope_theta=10000.0, max_pos=1024)
-    assert api.gemm_plan(8, 2 * ffn, d_model)["cfg"] == api.GEMM_SKINNY
-    assert api.gemm_plan(9, 2 * ffn, d_model)["cfg"] != api.GEMM_SKINNY
+    assert api.gemm_plan(8, 2 * ffn, d_model)["cfg"] == api.GEMM_STREAM
+    assert api.gemm_plan(9, 2 * ffn, d_model)["cfg"] != api.GEMM_STREAM
     sess = Session(shape, num_blocks=16, max_c=0, max_b=8, device_weights=True)
     for sid in range(8):
         sess.ctx.seq_create(sid)

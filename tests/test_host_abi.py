@@ -289,10 +289,10 @@ def test_batched_prefill_validation_through_abi():
 @pytest.mark.parametrize("shape", ["8b", "tiny"])
 def test_gemm_plan_is_valid_for_every_row_count(shape):
     """The planner's choice for every row count is a launchable plan: tile
-    widths divide n, the k split divides k into whole 64-deep steps, stream-K
-    only with whole tiles counted in rounds of 8 XCDs, the weight-streaming
-    kernel only up to 32 rows, the narrow kernel only up to 24 with k split
-    into whole 32-wide slices over at most eight waves."""
+    widths divide n, the k split divides k into whole 64-deep steps, the
+    weight-streaming kernel only for gate/up, up to 8 rows and at the sizes it
+    is built for, the narrow kernel only up to 24 with k split into whole
+    32-wide slices over at most eight waves."""
     sh = synth.LLAMA8B_LAYER if shape == "8b" else synth.TINY
     d, F = sh.d_model, sh.ffn_dim
     qkv = (sh.n_q_heads + 2 * sh.n_kv_heads) * sh.head_dim
@@ -302,23 +302,33 @@ def test_gemm_plan_is_valid_for_every_row_count(shape):
             continue
         for m in list(range(1, 600)) + list(range(600, 9000, 37)):
             p = api.gemm_plan(m, n, k)
-            if p["cfg"] == api.GEMM_SKINNY:
-                assert m <= 32
+            assert p["other_cfg"] != api.GEMM_STREAM
+            if p["cfg"] == api.GEMM_STREAM:
+                assert m <= 8 and n == 2 * F and n >= 16384 and k % 512 == 0 and 1024 <= k <= 8192
                 continue
+            assert (p["cfg"], p["splits"]) == (p["other_cfg"], p["other_splits"])
             if p["cfg"] == api.GEMM_NARROW:
                 assert m <= 24 and n % 64 == 0 and k % 32 == 0 and p["bn"] == 16 and p["splits"] == 1
                 seen.add(p["cfg"])
                 continue
             assert n % p["bn"] == 0 and p["bm"] % 32 == 0
             assert p["splits"] in (1, 2, 4, 8) and k % (64 * p["splits"]) == 0
-            if p["sk_workers"]:
-                assert p["splits"] == 1 and p["dp_tiles"] % 8 == 0 and 0 < p["sk_workers"] <= 512
             seen.add(p["cfg"])
     assert len(seen) >= 2
     with pytest.raises(api.SloweaveError):
         api.gemm_plan(0, 4096, 4096)
     with pytest.raises(api.SloweaveError):
         api.gemm_plan(64, 4000, 4096)
+
+
+def test_gemm_plan_of_a_wide_projection_that_is_not_gate_up():
+    """A qkv projection as wide as a gate/up one (160 heads of 128) never gets
+    the weight-streaming kernel, whose epilogue is SwiGLU: the plan names the
+    tile kernel for it, with a split it can divide k by."""
+    for m in range(1, 9):
+        p = api.gemm_plan(m, 160 * 128, 4096)
+        assert p["cfg"] == api.GEMM_STREAM and 0 <= p["other_cfg"] < api.GEMM_NARROW
+        assert 4096 % (64 * p["other_splits"]) == 0
 
 
 def _share(total, slots, quantum):
