@@ -10,7 +10,6 @@ typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -24,13 +23,6 @@ __device__ __forceinline__ bf16 f2bf(float v) { return static_cast<bf16>(v); }  
 // element i: row 4 * (l / 16) + i, column l % 16.
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// 32x32x16 bf16 MFMA.  Lane l supplies row / column l % 32 and the eight k
-// values of group l / 32; element i of the result in lane l is
-// row 8 * (i / 4) + 4 * (l / 32) + i % 4, column l % 32.
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
 // Work-groups of a launch are dispatched round-robin to the 8 XCDs (linear id

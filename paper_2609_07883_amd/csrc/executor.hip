@@ -202,6 +202,11 @@ struct LayerPlans {
     size_t partial_bytes() const {
         return std::max(std::max(qkv.partial_bytes, o.partial_bytes), std::max(gu.partial_bytes, d.partial_bytes));
     }
+    bool ok(const slw_model_cfg& c, int M) const {
+        return gemm_plan_ok(qkv, M, qkv_width(c), c.d_model, false) &&
+               gemm_plan_ok(o, M, c.d_model, c.n_q_heads * c.head_dim, false) &&
+               gemm_plan_ok(gu, M, 2 * c.ffn_dim, c.d_model, true) && gemm_plan_ok(d, M, c.d_model, c.ffn_dim, false);
+    }
 };
 
 LayerPlans plan_layer(const slw_model_cfg& c, int M) {
@@ -353,6 +358,7 @@ int mixed_iteration_impl(slw_ctx* ctx, const slw_batch* bt, const void* x_in, vo
     }
     Layout L = layout(c, C, B);
     const LayerPlans plans = plan_layer(c, C + B);
+    if (!plans.ok(c, C + B)) return fail(SLW_EINVAL, "internal: GEMM plan");
     size_t need = L.end_fixed + plans.partial_bytes();
     // The static array also takes an iteration whose split-K partials alone
     // would not fit: they then share the room of the attention partials, which

@@ -35,14 +35,14 @@ __device__ __forceinline__ int qkv_dim(int cw, int hd) {
     return ((((b & 1) << 1) | (b >> 1)) << 5) | (cw & 31);
 }
 
-// Rotate (x0, x1) = dims (d0, d0 + hd/2) of head hg of row `row` by
-// cs = (cos, sin) (q and k heads; v heads are not rotated) and store; k and v
-// also go to their KV page at slot[row].
-__device__ __forceinline__ void qkv_store_cs(const GemmArgs& g, int row, int hg, int d0, float x0, float x1,
-                                             float2 cs, int slot) {
-    const int d1 = d0 + g.hd / 2;
+// Rotate (x0, x1) = dims (d0, d0 + hd/2) of head hg of row `row` by the
+// iteration's table (q and k heads; v heads are not rotated) and store; k and
+// v also go to their KV page at slot[row].
+__device__ __forceinline__ void qkv_store(const GemmArgs& g, int row, int hg, int d0, float x0, float x1) {
+    const int d1 = d0 + g.hd / 2, slot = hg < g.hq ? 0 : g.slot[row];
     bf16* out = static_cast<bf16*>(g.out) + static_cast<size_t>(row) * g.ldo + hg * g.hd;
     if (hg < g.hq + g.hkv) {
+        const float2 cs = g.rope_cs[row * (g.hd / 2) + d0];
         const float y0 = x0 * cs.x - x1 * cs.y;
         const float y1 = x1 * cs.x + x0 * cs.y;
         x0 = y0;
@@ -62,12 +62,6 @@ __device__ __forceinline__ void qkv_store_cs(const GemmArgs& g, int row, int hg,
         pg[d0 * 16 + t] = b0;
         pg[d1 * 16 + t] = b1;
     }
-}
-
-// The same with the rotation and the slot read from the iteration's tables.
-__device__ __forceinline__ void qkv_store(const GemmArgs& g, int row, int hg, int d0, float x0, float x1) {
-    const float2 cs = hg < g.hq + g.hkv ? g.rope_cs[row * (g.hd / 2) + d0] : make_float2(1.f, 0.f);
-    qkv_store_cs(g, row, hg, d0, x0, x1, cs, hg < g.hq ? 0 : g.slot[row]);
 }
 
 // Tile (tm, tn) at position t of the grouped tile order: group_m tile rows
@@ -835,8 +829,7 @@ __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(GemmArgs g
     }
 }
 
-// Tile configurations: rows, columns, waves along each, work-groups that share
-// a CU, and the planner's time per 64-deep k step of one work-group (us).
+// Tile configurations: rows, columns, work-groups that share a CU, and the planner's time per 64-deep k step of one work-group (us).
 struct TileCfg {
     int bm, bn, per_cu;
     float step_us;
@@ -916,9 +909,10 @@ void launch_narrow(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
 // work-groups over the CUs, each a fixed cost (fill of the LDS buffers,
 // epilogue, which grows with the tile) plus its k steps; where two work-groups
 // share a CU, a round of both takes about twice as long as one alone.  Against
-// that stands the time to stream the weights (a CU draws at most 32 KB/us, the
-// chip 6.7 TB/s) and to bring every tile's panels from L2 (smooth maximum); a
-// split adds its reduction's launch and traffic.  Rows count in blocks of 32
+// that stands the time to stream the weights and to bring every tile's panels
+// from L2 (smooth maximum; its rates are free parameters of the fit, above what
+// a plain read reaches: 5.7-5.9 TB/s, 23 KB/us and CU); a split adds its
+// reduction's launch and traffic.  Rows count in blocks of 32
 // (every tile's row granularity), so that row counts of one block share a plan.
 // The constants are a fit to 3500 timings (eleven shapes, 16 to 4104 rows, all
 // configurations, splits 1 to 8; activations in cache, weights cycled through
@@ -1021,10 +1015,10 @@ GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k) {
     return p;
 }
 
-bool gemm_shape_ok(const GemmPlan& p, int n, int k) {
-    if (p.cfg == kNarrowCfg)  // m <= 32 is the caller's part; paired epilogues need 64-column tiles
-        return n % 64 == 0 && p.ks >= 1 && p.ks <= 8 && k % (32 * p.ks) == 0;
-    if (p.cfg == kStreamCfg) return n % 16 == 0 && stream_shape_ok(n, k);  // m <= 8 and the SwiGLU epilogue are the caller's part
+bool gemm_plan_ok(const GemmPlan& p, int m, int n, int k, bool swiglu) {
+    if (p.cfg == kNarrowCfg)  // paired epilogues need 64-column tiles
+        return m <= 32 && n % 64 == 0 && p.ks >= 1 && p.ks <= kNarrowMaxWaves && k % (32 * p.ks) == 0;
+    if (p.cfg == kStreamCfg) return swiglu && m <= kStreamMaxRows && n % 16 == 0 && stream_shape_ok(n, k);
     return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 

@@ -52,8 +52,8 @@ constexpr int kNarrowCfg = 98;  // the narrow kernel (m <= 32, k split inside th
 GemmPlan plan_gemm(int m, int n, int k, bool swiglu);
 // The plan for a given configuration and k split.
 GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k);
-// Whether the plan's tiles divide n and its splits k.
-bool gemm_shape_ok(const GemmPlan& p, int n, int k);
+// Whether the plan's kernel is built for the product: rows, tiles that divide n, splits that divide k.
+bool gemm_plan_ok(const GemmPlan& p, int m, int n, int k, bool swiglu);
 // Enqueue the GEMM.  A plan with splits > 1 writes partial sums to `partial`,
 // `partial_bytes` of them: fewer than plan.partial_bytes (but those of one row
 // at least) make it run in blocks of rows one after the other, with the same results.
