@@ -169,7 +169,7 @@ def test_policy_variants_on_gpu(setup):
     measured table alone (interactive D = 4 T_hat(1, 0), admitted while the
     decode batch they join costs at most halfway between the cheapest and the
     dearest decode-only row; batch D 20x larger)."""
-    sess, ct, tr = setup
+    sess, ct, _ = setup
     t_dec = ct.lookup(1, 0)
     n = 12
     burst = synth.RequestTrace(np.full(n, 1000, np.int64), np.arange(20, 20 + 7 * n, 7, dtype=np.int64),
@@ -193,6 +193,12 @@ def test_policy_variants_on_gpu(setup):
             admitted += 1
     assert [i for i in range(n) if res.token_ns[i][0] < 0] == expect and refused == len(expect) > 0
     # aging: a D below one decode-only iteration leaves no admissible chunk
+    # beside a decode.  The first prompt of a simultaneous burst runs alone and
+    # then decodes 63 tokens, so the others wait past 2 T_hat(1, 0) however
+    # fast the iterations are.
+    n = 6
+    tr = synth.RequestTrace(np.full(n, 1000, np.int64), np.arange(50, 50 + 30 * n, 30, dtype=np.int64),
+                            np.full(n, 64, np.int64))
     res = serving.run(tr, policy="sloweave", tpot_ms=0.5 * t_dec / 1e6, max_decode=16, c_max=256, table=ct,
                       session=sess, aging_ns=int(2 * t_dec), aging_chunk=32)
     torch.cuda.synchronize()
