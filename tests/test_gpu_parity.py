@@ -67,10 +67,9 @@ def test_tiny_prompt_in_chunks_with_decodes(tiny_sessions, qk_std):
         stream += 1
 
 
-def test_tiny_long_chunk_stream_k():
-    """903 rows (a 900-token chunk at prefix 100 and three decodes): the
-    output projection (256 x 256 wide) runs the stream-K schedule, whose
-    pieces and fixup must reproduce every row."""
+def test_tiny_long_chunk():
+    """903 rows (a 900-token chunk at prefix 100 and three decodes): many row
+    tiles of narrow projections, the last one ragged."""
     _require_gpu()
     from paper_2609_07883_amd.runtime import Session
     sess = Session(synth.TINY, num_blocks=512, max_c=1024, max_b=4, qk_std=0.16)
@@ -92,11 +91,10 @@ def test_tiny_long_chunk_stream_k():
 
 
 @pytest.mark.parametrize("C", [100, 150, 600, 850, 1000])
-def test_tiny_gemm_plan_bands(C):
-    """Row counts in several of the GEMM planner's bands on the Tiny shapes
-    (narrow projections: the tile fallbacks for widths that are not a
-    multiple of 256, forced splits refused where k does not divide): every
-    row of the iteration against the oracle."""
+def test_tiny_row_counts(C):
+    """Several row counts on the Tiny shapes, whose narrow projections all
+    take 64 x 128 tiles and are too short in k to be split: every row of the
+    iteration against the oracle."""
     _require_gpu()
     from paper_2609_07883_amd.runtime import Session
     sess = Session(synth.TINY, num_blocks=512, max_c=1024, max_b=4, qk_std=0.16)
