@@ -255,7 +255,13 @@ int slw_workspace_view(slw_ctx* ctx, int32_t which, int32_t C, int32_t B, size_t
  * Stages absent from that iteration (C == 0 or B == 0) read 0.  Stage 1 is
  * kept for the layout of the array and reads (close to) 0: the RoPE table is
  * filled by the iteration's first kernel, together with the metadata copy,
- * before stage 0 of layer 0.
+ * before stage 0 of layer 0.  Where gate/up streams its weights (configuration
+ * 99 of slw_gemm_plan, C + B <= 8) that kernel applies the RMSNorm before it:
+ * stage 7 then reads (close to) 0 and its work is part of stage 8.
+ * Recording changes what is launched, not what is computed: the first layer's
+ * RMSNorm, otherwise part of the iteration's first kernel, is a launch of its
+ * own, and so is decode attention beside a chunk, so that the stages of a
+ * recorded iteration add up to a little more than an unrecorded one takes.
  */
 #define SLW_N_STAGES 10
 int slw_set_stage_timing(slw_ctx* ctx, int32_t depth);
