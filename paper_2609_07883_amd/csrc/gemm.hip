@@ -120,8 +120,9 @@ __device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" ::: "m
 // 16 x 16 x 32 MFMAs, weights as the A operand; k advances 64 at a time
 // through two LDS buffers per operand.
 //
-// What bounds it: at the largest tile the chip runs into its power limit (the
-// same kernel on all-zero operands is 1.35 x faster), so the design saves
+// What bounds it: at the largest tile the chip runs into its power limit (on
+// all-zero operands the same kernel is 1.27 x faster: gate/up of the 8B layer
+// at 4096 rows 661 -> 520 us, 1455 -> 1850 TFLOP/s), so the design saves
 // energy per product as much as it hides latency: 16 x 16 x 32 MFMAs touch
 // the accumulators half as often per product as 32 x 32 x 16 (+9% at 4096 x
 // 28672 x 4096), every operand byte is read from LDS once per k step, and no
@@ -912,29 +913,31 @@ void launch_narrow(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
 // that stands the time to stream the weights and to bring every tile's panels
 // from L2 (smooth maximum; its rates are free parameters of the fit, above what
 // a plain read reaches: 5.7-5.9 TB/s, 23 KB/us and CU); a split adds its
-// reduction's launch and traffic.  Rows count in blocks of 32
-// (every tile's row granularity), so that row counts of one block share a plan.
-// The constants are a fit to 3500 timings (eleven shapes, 16 to 4104 rows, all
-// configurations, splits 1 to 8; activations in cache, weights cycled through
-// 700 MB so that none are: a layer finds them so, and fitted to weights in the
-// last-level cache the rule picked tiles 20-40% slower for the output and qkv
-// projections at 288 rows): median error below 1%, 90% within -11% and +13%;
-// the configuration it picks is on average 0.7% slower than the fastest one
-// measured, 18% at worst.
-float predict_us(const TileCfg& c, int splits, int m32, int n, int k) {
-    const int wgs = ((m32 + c.bm - 1) / c.bm) * (n / c.bn) * splits;
-    const float nk = static_cast<float>(k / 64) / splits;
+// reduction's launch and traffic.  Rows count in blocks of 32 (every tile's row
+// granularity), so that row counts of one block share a plan.  The constants are
+// a fit to 4200 timings (ten shapes, 16 to 4104 rows, all configurations,
+// splits 1 to 8; activations in cache, weights cycled through 700 MB so that
+// none are: a layer finds them so, and fitted to weights in the last-level cache
+// the rule picked tiles 20-40% slower for the output and qkv projections at 288
+// rows): median error below 1%, 90% within -11% and +13%; the configuration it
+// picks is on average 0.8% slower than the fastest one measured, 18% at worst.
+// `tiles`: of the configuration, `inv`: 1 / splits.  A configuration that cannot
+// come below `limit` is not priced to the end: every iteration prices some 60.
+float predict_us(const TileCfg& c, int tiles, int splits, float inv, int m32, int n, int k, float limit) {
+    const int wgs = tiles * splits;
+    const float nk = static_cast<float>(k / 64) * inv;
     const float fixed = 4.18f + 2.66f * (c.bm * c.bn) / 65536.f;
     const float one = fixed + nk * c.step_us, both = fixed + 1.91f * nk * c.step_us;
-    const int full = wgs / (kCus * c.per_cu), rem = wgs % (kCus * c.per_cu);
+    const int full = c.per_cu == 2 ? wgs / (2 * kCus) : wgs / kCus, rem = wgs - full * kCus * c.per_cu;
     float t = full * (c.per_cu == 2 ? both : one);
     if (rem) t += c.per_cu == 2 && rem > kCus ? both : one;
+    const float reduce = splits > 1 ? 2.18f + 8.f * splits * m32 * n / 4.68e6f : 0.f;
+    if (t + reduce >= limit) return limit;
     const float rate = std::min(6.73e6f, 32.0e3f * std::min(wgs, kCus));
-    const float mem = 2.f * n * k / rate + 0.2f + 2.f * wgs * (c.bm + c.bn) * (static_cast<float>(k) / splits) / 40.59e6f;
+    const float mem = 2.f * n * k / rate + 0.2f + 2.f * wgs * (c.bm + c.bn) * (static_cast<float>(k) * inv) / 40.59e6f;
+    if (mem + reduce >= limit) return limit;
     const float t2 = t * t, m2 = mem * mem;
-    t = 0.91f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2));
-    if (splits > 1) t += 2.18f + 8.f * splits * m32 * n / 4.68e6f;
-    return t;
+    return 0.91f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2)) + reduce;
 }
 
 // Whether a gate/up projection of few rows streams its weights (k of a size
@@ -975,12 +978,14 @@ GemmPlan plan_gemm(int m, int n, int k, bool swiglu) {
     if (!wide && m <= narrow_rows) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
     int cfg = kNumCfgs - 1, splits = 1;
     const int m32 = (m + 31) / 32 * 32;
-    float best = 0.f;
+    float best = HUGE_VALF;
     for (int c = 0; c < kNumCfgs; ++c) {
         if (n % kCfgs[c].bn) continue;
-        for (int sp = 1; sp <= kMaxSplits && (sp == 1 || (k % (64 * sp) == 0 && k / sp >= 512)); sp *= 2) {
-            const float t = predict_us(kCfgs[c], sp, m32, n, k);
-            if (best == 0.f || t < best) {
+        const int tiles = ((m32 + kCfgs[c].bm - 1) / kCfgs[c].bm) * (n / kCfgs[c].bn);
+        float inv = 1.f;
+        for (int sp = 1; sp <= kMaxSplits && (sp == 1 || (k % (64 * sp) == 0 && k / sp >= 512)); sp *= 2, inv *= 0.5f) {
+            const float t = predict_us(kCfgs[c], tiles, sp, inv, m32, n, k, best);
+            if (t < best) {
                 best = t;
                 cfg = c;
                 splits = sp;
