@@ -519,8 +519,9 @@ __global__ __launch_bounds__(512) void chunk_attn_kernel(ChunkAttnArgs a, Decode
 //
 // The same work, layouts and arithmetic as chunk_attn_kernel.  There, the two
 // waves of a SIMD meet at a barrier once a tile and run the same stage side by
-// side, so the matrix cores idle while both do softmax (MFMA busy 54%).  Here a
-// tile's work is two phases with a barrier after each:
+// side, so the matrix cores idle while both do softmax (busy 54% of the cycles
+// over the chunks of a 32 K prompt, 59% here).  Here a tile's work is two phases
+// with a barrier after each:
 //   P1(t)  mask, running max, exponentials, P in bf16        (VALU)
 //   P2(t)  P V of tile t, then the scores of tile t + 1      (matrix cores)
 // and waves 4-7 run one phase behind waves 0-3 (one extra barrier at an item's

@@ -120,13 +120,13 @@ __device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" ::: "m
 // 16 x 16 x 32 MFMAs, weights as the A operand; k advances 64 at a time
 // through two LDS buffers per operand.
 //
-// What bounds it: at the largest tile the chip runs into its power limit (on
-// all-zero operands the same kernel is 1.27 x faster: gate/up of the 8B layer
-// at 4096 rows 661 -> 520 us, 1455 -> 1850 TFLOP/s), so the design saves
-// energy per product as much as it hides latency: 16 x 16 x 32 MFMAs touch
-// the accumulators half as often per product as 32 x 32 x 16 (+9% at 4096 x
-// 28672 x 4096), every operand byte is read from LDS once per k step, and no
-// register staging is used.
+// What bounds it: at the largest tile the chip runs into its power limit (the
+// matrix cores are busy 72% of the cycles, and on all-zero operands the same
+// kernel is 1.27 x faster: gate/up of the 8B layer at 4096 rows 661 -> 520 us,
+// 1455 -> 1850 TFLOP/s), so the design saves energy per product as much as it
+// hides latency: 16 x 16 x 32 MFMAs touch the accumulators half as often per
+// product as 32 x 32 x 16 (+9% at 4096 x 28672 x 4096), every operand byte is
+// read from LDS once per k step, and no register staging is used.
 //
 // Schedule.  A wave's tile is cut into four quadrants: its A rows in two
 // halves (A0, A1), its B columns in two halves.  A k step runs four phases,
@@ -613,8 +613,8 @@ constexpr int stream_ring(int ns) {
         if (ns % r == 0) return r;
     return ns;
 }
-// k = 256 NS, NS even, from 4 to 32.
 
+// k = 256 NS, NS even, from 4 to 32.
 template <int NS>
 __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, int per_wg) {
     constexpr int R = stream_ring(NS);
@@ -830,7 +830,8 @@ __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(GemmArgs g
     }
 }
 
-// Tile configurations: rows, columns, work-groups that share a CU, and the planner's time per 64-deep k step of one work-group (us).
+// Tile configurations: rows, columns, work-groups that share a CU, and the
+// planner's time per 64-deep k step of one work-group (us).
 struct TileCfg {
     int bm, bn, per_cu;
     float step_us;
@@ -943,8 +944,8 @@ float predict_us(const TileCfg& c, int tiles, int splits, float inv, int m32, in
 // Whether a gate/up projection of few rows streams its weights (k of a size
 // the kernel is built for).  Multiples of 1024 from 2048 to 6144 do at any width.
 // The others do where the tile kernel stands badly: for k below 2048, and at
-// widths whose 128-column tiles leave its second round of work-groups less than half
-// full.  Norm and gate/up stages, tile kernel / streamed, us at 1 and 8 rows:
+// widths whose 128-column tiles leave its second round of work-groups less than
+// half full.  Norm and gate/up stages, tile kernel / streamed, us at 1 and 8 rows:
 // k 3584, n 37888: 71 / 62, 71 / 67; k 6656, n 37888: 125 / 102, 126 / 111;
 // k 7168, n 40960: 134 / 121, 134 / 130; k 1024, n 16384: 20 / 17, 20 / 17;
 // and outside, where it can lose: k 7168, n 28672: 79 / 91, 79 / 99.
