@@ -614,8 +614,11 @@ constexpr int stream_ring(int ns) {
     return ns;
 }
 
-// k = 256 NS, NS even, from 4 to 32.
-template <int NS>
+// A wave takes NS slices of 32 k, NS even, from 4 to 32: k = 256 NS, or with
+// TAIL any k of at most that and more than 256 (NS - 2), whose last one or two
+// slices are missing from some waves: those read another slice in their place
+// and multiply zeros.
+template <int NS, bool TAIL>
 __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, int per_wg) {
     constexpr int R = stream_ring(NS);
     static_assert(NS % R == 0, "a unit is whole turns of the ring");
@@ -624,7 +627,10 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
     const int lane = threadIdx.x & 63, ks = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int j = lane & 15, grp = lane >> 4;
     const int u0 = blockIdx.x * per_wg, u1 = min(u0 + per_wg, units);
-    const int kbeg = ks * NS * 32 + 8 * grp;
+    const int slices = g.k / 32, own = TAIL ? slices / 8 + (ks < slices % 8) : NS;
+    const int kbeg = (TAIL ? ks * (slices / 8) + min(ks, slices % 8) : ks * NS) * 32 + 8 * grp;
+    auto off = [&](int s) { return 32 * (TAIL && s >= NS - 2 ? min(s, own - 1) : s); };
+    auto missing = [&](int s) { return TAIL && s >= NS - 2 && s >= own; };
     // W row of this lane in unit u: rows 0 .. 7 of the MFMA take gate rows 8 u .. 8 u + 7, rows 8 .. 15 their up rows
     auto wptr = [&](int u) {
         const int row = 8 * u + (j & 7) + (j >> 3) * (g.n >> 1);
@@ -633,7 +639,7 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
     bf16x8 wf[R];
     const bf16* wp = wptr(u0);
 #pragma unroll
-    for (int s = 0; s < R; ++s) wf[s] = *reinterpret_cast<const bf16x8*>(wp + 32 * s);
+    for (int s = 0; s < R; ++s) wf[s] = *reinterpret_cast<const bf16x8*>(wp + off(s));
 
     // activations: row j (rows past m repeat row m - 1; their results are never
     // stored), read once and normalised in registers
@@ -643,7 +649,7 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
         // the scaling; longer ones are read twice
         constexpr bool KEEP = NS <= 24;
         const float* src = static_cast<const float*>(g.a) + static_cast<size_t>(min(j, g.m - 1)) * g.lda + kbeg;
-        auto half = [&](int s, int h) { return *reinterpret_cast<const f32x4*>(src + 32 * s + 4 * h); };
+        auto half = [&](int s, int h) { return *reinterpret_cast<const f32x4*>(src + off(s) + 4 * h); };
         f32x4 raw[KEEP ? NS : 1][2];
         float ss = 0.f;
         if constexpr (KEEP) {
@@ -658,13 +664,16 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
             else return half(s, h);
         };
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
+        for (int s = 0; s < NS; ++s) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const f32x4 v = x(s, h);
+                f32x4 v = x(s, h);
+                if (missing(s)) v = f32x4{};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ss += v[e] * v[e];
             }
+            if (!KEEP && s % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // else all reads are issued at once, and spill
+        }
         ss += __shfl_xor(ss, 16, 64);
         ss += __shfl_xor(ss, 32, 64);
         if (grp == 0) ssq[ks][j] = ss;
@@ -676,13 +685,15 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
         const float inv = 1.0f / sqrtf(tot / static_cast<float>(g.k) + g.norm_eps);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const bf16x8 gain = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(g.norm_g) + kbeg + 32 * s);
+            const bf16x8 gain = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(g.norm_g) + kbeg + off(s));
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const f32x4 v = x(s, h);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) af[s][4 * h + e] = f2bf(v[e] * inv * bf2f(gain[4 * h + e]));
             }
+            if (missing(s)) af[s] = bf16x8{};
+            if (!KEEP && s % 8 == 7) __builtin_amdgcn_sched_barrier(0);
         }
     }
 
@@ -693,9 +704,10 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
         f32x4 acc = {};
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            acc = mfma16(wf[s % R], af[s], acc);
-            if (s + R < NS) wf[s % R] = *reinterpret_cast<const bf16x8*>(wp + 32 * (s + R));
-            else if (MORE) wf[s % R] = *reinterpret_cast<const bf16x8*>(wn + 32 * (s + R - NS));
+            // both factors of a missing slice are zero: the other slice's weights may not be finite
+            acc = mfma16(missing(s) ? bf16x8{} : wf[s % R], af[s], acc);
+            if (s + R < NS) wf[s % R] = *reinterpret_cast<const bf16x8*>(wp + off(s + R));
+            else if (MORE) wf[s % R] = *reinterpret_cast<const bf16x8*>(wn + off(s + R - NS));
         }
         wp = wn;
         const int b = (u - u0) & 1;
@@ -868,12 +880,13 @@ void launch_cfg(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t
 
 template <int NS>
 void launch_stream_ns(const GemmArgs& g, hipStream_t s) {
-    const int units = g.n / 16, per = (units + kCus - 1) / kCus;
-    stream_kernel<NS><<<(units + per - 1) / per, 512, 0, s>>>(g, units, per);
+    const int units = g.n / 16, per = (units + kCus - 1) / kCus, wgs = (units + per - 1) / per;
+    if (g.k == 256 * NS) stream_kernel<NS, false><<<wgs, 512, 0, s>>>(g, units, per);
+    else stream_kernel<NS, true><<<wgs, 512, 0, s>>>(g, units, per);
 }
 
 void launch_stream(const GemmArgs& g, hipStream_t s) {
-    switch (g.k / 512) {  // stream_shape_ok
+    switch ((g.k + 511) / 512) {  // stream_shape_ok
         case 2: launch_stream_ns<4>(g, s); break;
         case 3: launch_stream_ns<6>(g, s); break;
         case 4: launch_stream_ns<8>(g, s); break;
@@ -941,16 +954,16 @@ float predict_us(const TileCfg& c, int tiles, int splits, float inv, int m32, in
     return 0.91f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2)) + reduce;
 }
 
-// Whether a gate/up projection of few rows streams its weights (k of a size
-// the kernel is built for).  Multiples of 1024 from 2048 to 6144 do at any width.
-// The others do where the tile kernel stands badly: for k below 2048, and at
-// widths whose 128-column tiles leave its second round of work-groups less than
-// half full.  Norm and gate/up stages, tile kernel / streamed, us at 1 and 8 rows:
-// k 3584, n 37888: 71 / 62, 71 / 67; k 6656, n 37888: 125 / 102, 126 / 111;
-// k 7168, n 40960: 134 / 121, 134 / 130; k 1024, n 16384: 20 / 17, 20 / 17;
-// and outside, where it can lose: k 7168, n 28672: 79 / 91, 79 / 99.
+// Whether a gate/up projection of few rows streams its weights.  Multiples of
+// 1024 from 2048 to 6144 do at any width.  Other k do where the tile kernel
+// stands badly: below 2048, and at widths whose 128-column tiles leave its second
+// round of work-groups less than half full.  Norm and gate/up stages, tile kernel
+// / streamed, us at 1 and 8 rows: k 3584, n 37888: 71 / 62, 71 / 67; k 6656, n
+// 37888: 125 / 102, 126 / 111; k 7168, n 40960: 134 / 121, 134 / 130; k 1024, n
+// 16384: 20 / 17, 20 / 17; and outside, where it can lose: k 7168, n 28672: 79 /
+// 91, 79 / 99.
 bool stream_shape_ok(int n, int k) {
-    if (k % 512 || k < 1024 || k > 8192) return false;
+    if (k % 64 || k < 1024 || k > 8192) return false;
     if (k % 1024 == 0 && k >= 2048 && k <= 6144) return true;
     const int tiles = n / 128;
     return 2 * tiles < 3 * kCus && (k < 2048 || tiles > kCus);

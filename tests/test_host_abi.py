@@ -304,7 +304,7 @@ def test_gemm_plan_is_valid_for_every_row_count(shape):
             p = api.gemm_plan(m, n, k)
             assert p["other_cfg"] != api.GEMM_STREAM
             if p["cfg"] == api.GEMM_STREAM:
-                assert m <= 8 and n == 2 * F and n >= 16384 and k % 512 == 0 and 1024 <= k <= 8192
+                assert m <= 8 and n == 2 * F and n >= 16384 and k % 64 == 0 and 1024 <= k <= 8192
                 continue
             assert (p["cfg"], p["splits"]) == (p["other_cfg"], p["other_splits"])
             if p["cfg"] == api.GEMM_NARROW:
