@@ -607,9 +607,10 @@ __device__ __forceinline__ int w_row(const GemmArgs& g, int c) {
 // 6144 do not fit the registers in fp32 and are read twice.
 // ---------------------------------------------------------------------------
 constexpr int kStreamMaxRows = 8;
-// slices in flight per wave, a divisor of the slices of a unit
+// slices in flight per wave, a divisor of the slices of a unit (14 against 7 of 14
+// and 28: 2-3% of a layer; longer ones than these gained nothing)
 constexpr int stream_ring(int ns) {
-    for (int r : {8, 10, 9, 7, 11, 13, 6})
+    for (int r : {8, 10, 9, 14, 11, 13, 6})
         if (ns % r == 0) return r;
     return ns;
 }
@@ -954,19 +955,21 @@ float predict_us(const TileCfg& c, int tiles, int splits, float inv, int m32, in
     return 0.91f + std::sqrt(std::sqrt(t2 * t2 + m2 * m2)) + reduce;
 }
 
-// Whether a gate/up projection of few rows streams its weights.  Multiples of
-// 1024 from 2048 to 6144 do at any width.  Other k do where the tile kernel
-// stands badly: below 2048, and at widths whose 128-column tiles leave its second
-// round of work-groups less than half full.  Norm and gate/up stages, tile kernel
-// / streamed, us at 1 and 8 rows: k 3584, n 37888: 71 / 62, 71 / 67; k 6656, n
-// 37888: 125 / 102, 126 / 111; k 7168, n 40960: 134 / 121, 134 / 130; k 1024, n
-// 16384: 20 / 17, 20 / 17; and outside, where it can lose: k 7168, n 28672: 79 /
-// 91, 79 / 99.
-bool stream_shape_ok(int n, int k) {
-    if (k % 64 || k < 1024 || k > 8192) return false;
+// Whether a gate/up projection of up to 8 rows streams its weights.  Multiples
+// of 1024 from 2048 to 6144 do at any width.  Other k do where the tile kernel
+// stands badly: below 2048, and at widths whose 128-column tiles fill half of its
+// second round of work-groups or less; towards that end rows that have to be read
+// twice stay below 5.  Norm and gate/up stages, tile kernel / streamed, us at 1
+// and 8 rows: k 3584, n 37888: 71 / 59, 71 / 63; k 6656, n 37888: 125 / 101, 126
+// / 111; k 7168, n 40960: 134 / 117, 134 / 126; k 1024, n 16384: 20 / 17, 20 / 17;
+// k 6912, n 49152, the whole layer at 1 and 8 rows: 249 / 245, 277 / 282; and
+// outside, where it can lose: k 7168, n 28672: 79 / 91, 79 / 99.
+bool stream_shape_ok(int m, int n, int k) {
+    if (m > kStreamMaxRows || k % 64 || k < 1024 || k > 8192) return false;
     if (k % 1024 == 0 && k >= 2048 && k <= 6144) return true;
     const int tiles = n / 128;
-    return 2 * tiles < 3 * kCus && (k < 2048 || tiles > kCus);
+    if (2 * tiles > 3 * kCus || (8 * tiles > 11 * kCus && k > 6144 && m > 4)) return false;
+    return k < 2048 || tiles > kCus;
 }
 
 }  // namespace
@@ -987,7 +990,7 @@ bool stream_shape_ok(int n, int k) {
 // of 128 and k of 64; a split keeps at least 512 of k.
 GemmPlan plan_gemm(int m, int n, int k, bool swiglu) {
     const bool wide = n >= 16384, qkv_like = n >= 6144 && !wide;
-    if (swiglu && wide && m <= kStreamMaxRows && stream_shape_ok(n, k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
+    if (swiglu && wide && stream_shape_ok(m, n, k)) return plan_with_cfg(kStreamCfg, 1, m, n, k);
     const int narrow_rows = qkv_like || k >= 8192 ? 8 : n <= 3072 && k >= 1024 ? 32 : 24;
     if (!wide && m <= narrow_rows) return plan_with_cfg(kNarrowCfg, 1, m, n, k);
     int cfg = kNumCfgs - 1, splits = 1;
@@ -1037,7 +1040,7 @@ GemmPlan plan_with_cfg(int cfg, int splits, int m, int n, int k) {
 bool gemm_plan_ok(const GemmPlan& p, int m, int n, int k, bool swiglu) {
     if (p.cfg == kNarrowCfg)  // paired epilogues need 64-column tiles
         return m <= 32 && n % 64 == 0 && p.ks >= 1 && p.ks <= kNarrowMaxWaves && k % (32 * p.ks) == 0;
-    if (p.cfg == kStreamCfg) return swiglu && m <= kStreamMaxRows && n % 16 == 0 && stream_shape_ok(n, k);
+    if (p.cfg == kStreamCfg) return swiglu && n % 16 == 0 && stream_shape_ok(m, n, k);
     return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 

@@ -44,7 +44,7 @@ def test_few_rows(d_model):
 
 
 # multiples of 1024 from 2048 to 6144 stream at any width from 16384 on; the
-# others where 128-column tiles are 257 to 383 (n = 2 ffn), below 2048 also
+# others where 128-column tiles are 257 to 384 (n = 2 ffn), below 2048 also
 # fewer.  A hidden size for every number of slices a wave takes: the multiples
 # of 512, where all waves take as many, and others, where the last slices are
 # missing from all waves or from four of the eight.
@@ -52,7 +52,7 @@ SIZES = [(1024, 8256), (1536, 8256), (2048, 8256), (2560, 16448), (3072, 8256), 
          (4608, 16448), (5120, 8256), (5632, 16448), (6144, 8256), (6656, 17920), (7168, 16448), (7680, 16448),
          (8192, 16448), (1152, 8256), (1920, 8256), (2176, 16448), (2816, 19200), (3328, 18944), (3840, 19200),
          (4224, 17920), (4864, 16448), (5376, 16448), (5888, 16448), (6272, 16448), (6912, 16448), (7296, 16448),
-         (7936, 16448), (1408, 8256)]
+         (7936, 16448), (1408, 8256), (3584, 24576)]
 
 
 @pytest.mark.parametrize("d_model,ffn", SIZES)
