@@ -814,14 +814,8 @@ int enqueue_iteration(slw_ctx* ctx, const slw_batch* bt, const void* x_in, void*
         const bool gu_norm = plans.gu.cfg == kStreamCfg;  // that kernel normalises its rows itself
         if (!gu_norm) launch_rmsnorm(hbuf, true, wl.g2, xn, M, d, c.rms_eps, stream);
         if ((rc = mark(l, 8))) return rc;
-        {
-            GemmArgs ga{gu_norm ? hbuf : xn, wl.wgu, act, nullptr, M, 2 * F, d, d, F, EPI_SWIGLU};
-            if (gu_norm) {
-                ga.norm_g = wl.g2;
-                ga.norm_eps = c.rms_eps;
-            }
-            launch_gemm(ga, plans.gu, gpartp, L.gemm_part_bytes, stream);
-        }
+        launch_gemm(GemmArgs{gu_norm ? hbuf : xn, wl.wgu, act, nullptr, M, 2 * F, d, d, F, EPI_SWIGLU}, plans.gu,
+                    gpartp, L.gemm_part_bytes, stream, {wl.g2, c.rms_eps});
         if ((rc = mark(l, 9))) return rc;
         launch_gemm(GemmArgs{act, wl.wd, x_out, hbuf, M, d, F, F, d, EPI_RESID_F32IN}, plans.d, gpartp,
                     L.gemm_part_bytes, stream);

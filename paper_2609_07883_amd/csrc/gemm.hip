@@ -620,7 +620,7 @@ constexpr int stream_ring(int ns) {
 // slices are missing from some waves: those read another slice in their place
 // and multiply zeros.
 template <int NS, bool TAIL>
-__global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, int per_wg) {
+__global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, NormArgs norm, int units, int per_wg) {
     constexpr int R = stream_ring(NS);
     static_assert(NS % R == 0, "a unit is whole turns of the ring");
     __shared__ f32x4 red[2][8][64];
@@ -683,10 +683,10 @@ __global__ __launch_bounds__(512, 2) void stream_kernel(GemmArgs g, int units, i
         float tot = 0.f;
 #pragma unroll
         for (int w = 0; w < 8; ++w) tot += ssq[w][j];
-        const float inv = 1.0f / sqrtf(tot / static_cast<float>(g.k) + g.norm_eps);
+        const float inv = 1.0f / sqrtf(tot / static_cast<float>(g.k) + norm.eps);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const bf16x8 gain = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(g.norm_g) + kbeg + off(s));
+            const bf16x8 gain = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(norm.gain) + kbeg + off(s));
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const f32x4 v = x(s, h);
@@ -880,29 +880,29 @@ void launch_cfg(const GemmArgs& g, const GemmPlan& p, void* partial, hipStream_t
 }
 
 template <int NS>
-void launch_stream_ns(const GemmArgs& g, hipStream_t s) {
+void launch_stream_ns(const GemmArgs& g, const NormArgs& norm, hipStream_t s) {
     const int units = g.n / 16, per = (units + kCus - 1) / kCus, wgs = (units + per - 1) / per;
-    if (g.k == 256 * NS) stream_kernel<NS, false><<<wgs, 512, 0, s>>>(g, units, per);
-    else stream_kernel<NS, true><<<wgs, 512, 0, s>>>(g, units, per);
+    if (g.k == 256 * NS) stream_kernel<NS, false><<<wgs, 512, 0, s>>>(g, norm, units, per);
+    else stream_kernel<NS, true><<<wgs, 512, 0, s>>>(g, norm, units, per);
 }
 
-void launch_stream(const GemmArgs& g, hipStream_t s) {
+void launch_stream(const GemmArgs& g, const NormArgs& norm, hipStream_t s) {
     switch ((g.k + 511) / 512) {  // stream_shape_ok
-        case 2: launch_stream_ns<4>(g, s); break;
-        case 3: launch_stream_ns<6>(g, s); break;
-        case 4: launch_stream_ns<8>(g, s); break;
-        case 5: launch_stream_ns<10>(g, s); break;
-        case 6: launch_stream_ns<12>(g, s); break;
-        case 7: launch_stream_ns<14>(g, s); break;
-        case 8: launch_stream_ns<16>(g, s); break;
-        case 9: launch_stream_ns<18>(g, s); break;
-        case 10: launch_stream_ns<20>(g, s); break;
-        case 11: launch_stream_ns<22>(g, s); break;
-        case 12: launch_stream_ns<24>(g, s); break;
-        case 13: launch_stream_ns<26>(g, s); break;
-        case 14: launch_stream_ns<28>(g, s); break;
-        case 15: launch_stream_ns<30>(g, s); break;
-        default: launch_stream_ns<32>(g, s); break;
+        case 2: launch_stream_ns<4>(g, norm, s); break;
+        case 3: launch_stream_ns<6>(g, norm, s); break;
+        case 4: launch_stream_ns<8>(g, norm, s); break;
+        case 5: launch_stream_ns<10>(g, norm, s); break;
+        case 6: launch_stream_ns<12>(g, norm, s); break;
+        case 7: launch_stream_ns<14>(g, norm, s); break;
+        case 8: launch_stream_ns<16>(g, norm, s); break;
+        case 9: launch_stream_ns<18>(g, norm, s); break;
+        case 10: launch_stream_ns<20>(g, norm, s); break;
+        case 11: launch_stream_ns<22>(g, norm, s); break;
+        case 12: launch_stream_ns<24>(g, norm, s); break;
+        case 13: launch_stream_ns<26>(g, norm, s); break;
+        case 14: launch_stream_ns<28>(g, norm, s); break;
+        case 15: launch_stream_ns<30>(g, norm, s); break;
+        default: launch_stream_ns<32>(g, norm, s); break;
     }
 }
 
@@ -1044,7 +1044,8 @@ bool gemm_plan_ok(const GemmPlan& p, int m, int n, int k, bool swiglu) {
     return p.cfg >= 0 && p.cfg < kNumCfgs && n % p.bn == 0 && k % (p.splits * 64) == 0;
 }
 
-void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, size_t partial_bytes, hipStream_t s) {
+void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, size_t partial_bytes, hipStream_t s,
+                 const NormArgs& norm) {
     if (g.m <= 0) return;
     const size_t row_bytes = static_cast<size_t>(p.splits) * g.n * sizeof(float);
     if (p.splits > 1 && g.m * row_bytes > partial_bytes) {
@@ -1074,7 +1075,7 @@ void launch_gemm(const GemmArgs& g, const GemmPlan& p, void* partial, size_t par
         return;
     }
     if (p.cfg == kStreamCfg) {
-        launch_stream(g, s);
+        launch_stream(g, norm, s);
         return;
     }
     switch (p.cfg) {  // kCfgs order
